@@ -19,11 +19,10 @@
 using namespace eamfe;
 
 // Scratch of eamfe_adjoint_theta_noalloc, for callers that cannot allocate:
-// the adjoint's fixed-point coefficient bins, then the knot transform's work
-// rows.  Each device holds its own copy from the library's load to the end
-// of the process; host code reaches it only through the address
-// hipGetSymbolAddress returns on that device (g_scratch_ptr), never through
-// this name.
+// the adjoint's fixed-point coefficient bins.  Each device holds its own copy
+// from the library's load to the end of the process; host code reaches it
+// only through the address hipGetSymbolAddress returns on that device
+// (g_scratch_ptr), never through this name.
 constexpr size_t kNoAllocScratchBytes = (size_t)32 << 20;
 static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes];
 constexpr int kMaxDevices = 64;
@@ -146,8 +145,8 @@ struct eamfe_ctx {
     int64_t replays = 0;
     DevBuf snap_P, snap_Q, snap_v, snap_w, snap_rows;
 
-    // adjoint: densities, fixed-point bins, finish scratch, weights
-    DevBuf rho_d, bins_d, adj_scratch_d, adj_w_d;
+    // adjoint: densities, fixed-point bins, weights
+    DevBuf rho_d, bins_d, adj_w_d;
     // sampling of dU/dtheta inside run_switching (0 = off)
     int adj_every = 0;
     int adj_reduce = 0;
@@ -274,7 +273,6 @@ void for_regions(eamfe_ctx* c, const Shape& s, F&& f)
     if (N && s.n_r) {
         const size_t nb = (size_t)std::max(s.n_r, s.n_rho) - 1;
         f(c->bins_d, G_ADJ, R * 3 * nb * 4 * sizeof(unsigned long long));
-        f(c->adj_scratch_d, G_ADJ, R * 3 * 2 * (nb + 1) * d);
     }
 }
 
@@ -910,14 +908,20 @@ int check_adjoint_tables(eamfe_ctx* c, const char* who)
 
 // dU/dtheta at the packed positions P (density pass already run with
 // rho_out, so F' and rho are current): bins -> knot gradients into out.
-// bins: n_rep * 3 * nb * 4 fixed-point words; fin: the knot transform's
-// work rows, (reduce ? 1 : n_rep) * 3 * 2 * (nb + 1) doubles.
+// bins: n_rep * 3 * nb * 4 fixed-point words.
 int adjoint_at(eamfe_ctx* c, const double4* P, const double* w_host, int reduce, double* out,
-               unsigned long long* bins_p, double* fin_p)
+               unsigned long long* bins_p)
 {
     OK(check_adjoint_tables(c, "adjoint"));
     const int nb = std::max(c->n_r, c->n_rho) - 1;
     const size_t bins = (size_t)c->n_rep * 3 * nb * 4;
+    const double* wd = nullptr;
+    if (w_host) {
+        HIPCHK(c, hipMemcpyAsync(c->adj_w_d.p, w_host, (size_t)c->n_rep * sizeof(double), hipMemcpyHostToDevice,
+                                 c->stream));
+        HIPCHK(c, hipStreamSynchronize(c->stream));   // the host array may go away
+        wd = (const double*)c->adj_w_d.p;
+    }
     LCHK(c, launch_fill_u64(bins_p, bins, 0ull, c->stream));   // a fill kernel: capturable, unlike a memset
     AdjointArgs a{};
     a.reps = (const RepDesc*)c->reps_d.p;
@@ -936,14 +940,7 @@ int adjoint_at(eamfe_ctx* c, const double4* P, const double* w_host, int reduce,
     a.n_units = c->n_tiles;
     const int grid = std::max(1, std::min(c->n_tiles, 2 * c->n_cu));
     LCHK(c, launch_adjoint(a, c->precision, grid, c->stream));
-    const double* wd = nullptr;
-    if (w_host) {
-        HIPCHK(c, hipMemcpyAsync(c->adj_w_d.p, w_host, (size_t)c->n_rep * sizeof(double), hipMemcpyHostToDevice,
-                                 c->stream));
-        HIPCHK(c, hipStreamSynchronize(c->stream));   // the host array may go away
-        wd = (const double*)c->adj_w_d.p;
-    }
-    LCHK(c, launch_adjoint_finish(a, wd, reduce, out, fin_p, c->stream));
+    LCHK(c, launch_adjoint_finish(a, wd, reduce, out, c->stream));
     return EAMFE_OK;
 }
 
@@ -1023,7 +1020,7 @@ int one_iteration(eamfe_ctx* c, StepArgs& a, double4* cur, double4* nxt, bool ha
     a.finish_prev = 0;
     if (sample) {
         OK(adjoint_at(c, cur, c->adj_w.empty() ? nullptr : c->adj_w.data(), c->adj_reduce, c->adj_out,
-                      (unsigned long long*)c->bins_d.p, (double*)c->adj_scratch_d.p));
+                      (unsigned long long*)c->bins_d.p));
         ++c->adj_samples;
     }
     OK(stamps(c, 1, &t0, &t1));
@@ -1127,12 +1124,12 @@ int iterate(eamfe_ctx* c, StepArgs a, double4** cur_io, bool has_eam, int64_t it
 
 bool ready(eamfe_ctx* c, bool need_pot);
 
-// dU/dtheta at positions x.  The adjoint's bins and knot-transform rows are
-// the context's own (static_base null), or at static_base and static_base +
-// fin_off.  The context's are looked up only after the lists are in place:
-// planning the lists can move the adjoint group of the arena.
+// dU/dtheta at positions x.  The adjoint's bins are the context's own
+// (static_bins null), or at static_bins.  The context's are looked up only
+// after the lists are in place: planning the lists can move the adjoint group
+// of the arena.
 int adjoint_theta_with(eamfe_ctx* c, const double* x, const double* w_host, int reduce, double* dtheta,
-                       char* static_base, size_t fin_off)
+                       unsigned long long* static_bins)
 {
     OK(check_adjoint_tables(c, "adjoint_theta"));   // before any kernel runs
     OK(pack(c, x));
@@ -1146,9 +1143,8 @@ int adjoint_theta_with(eamfe_ctx* c, const double* x, const double* w_host, int 
     a.step_kernel = 0;
     a.rho_out = (double*)c->rho_d.p;
     LCHK(c, launch_density(a, c->precision, c->lanes, c->block, c->stream));
-    unsigned long long* bins = static_base ? (unsigned long long*)static_base : (unsigned long long*)c->bins_d.p;
-    double* fin = static_base ? (double*)(static_base + fin_off) : (double*)c->adj_scratch_d.p;
-    OK(adjoint_at(c, PA(c), w_host, reduce, dtheta, bins, fin));
+    unsigned long long* bins = static_bins ? static_bins : (unsigned long long*)c->bins_d.p;
+    OK(adjoint_at(c, PA(c), w_host, reduce, dtheta, bins));
     return read_status(c);
 }
 
@@ -1768,7 +1764,7 @@ int eamfe_adjoint_theta(eamfe_ctx* c, const double* x, const double* w_host, int
     if (!ready(c, true)) return c ? EAMFE_ESTATE : EAMFE_EINVAL;
     if (!x || !dtheta) return fail(c, EAMFE_EINVAL, "adjoint_theta: null argument");
     (void)hipSetDevice(c->device);
-    return adjoint_theta_with(c, x, w_host, reduce, dtheta, nullptr, 0);
+    return adjoint_theta_with(c, x, w_host, reduce, dtheta, nullptr);
 }
 
 int eamfe_adjoint_theta_noalloc(eamfe_ctx* c, const double* x, const double* w_host, int reduce, double* dtheta)
@@ -1779,6 +1775,7 @@ int eamfe_adjoint_theta_noalloc(eamfe_ctx* c, const double* x, const double* w_h
         return fail(c, EAMFE_EDEVICE, "adjoint_theta_noalloc: no scratch address for this device");
     const size_t nb = (size_t)std::max(c->n_r, c->n_rho) - 1;
     const size_t bins = (size_t)c->n_rep * 3 * nb * 4 * sizeof(unsigned long long);
+    // the region's documented limit counts knot-transform rows besides the bins
     const size_t fin = (size_t)(reduce ? 1 : c->n_rep) * 3 * 2 * (nb + 1) * sizeof(double);
     const size_t fin_off = (bins + 255) / 256 * 256;
     if (fin_off + fin > kNoAllocScratchBytes)
@@ -1786,9 +1783,8 @@ int eamfe_adjoint_theta_noalloc(eamfe_ctx* c, const double* x, const double* w_h
                                          " bytes of scratch, more than its fixed " +
                                          std::to_string(kNoAllocScratchBytes) + " (fewer replicas or reduce = 1)");
     (void)hipSetDevice(c->device);
-    char* base = (char*)g_scratch_ptr[c->device];
     c->no_alloc = true;   // the arena must already hold the lists: report EAMFE_ENOMEM rather than grow it
-    const int rc = adjoint_theta_with(c, x, w_host, reduce, dtheta, base, fin_off);
+    const int rc = adjoint_theta_with(c, x, w_host, reduce, dtheta, (unsigned long long*)g_scratch_ptr[c->device]);
     c->no_alloc = false;
     return rc;
 }

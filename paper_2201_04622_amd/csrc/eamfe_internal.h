@@ -223,10 +223,9 @@ int launch_init_velocities(const StepArgs& a, int n_rep, int fix_com, hipStream_
 int launch_msd(const double* x, const double* x0, const RepDesc* reps, int n_rep, int N, double* out, hipStream_t s);
 int launch_adjoint(const AdjointArgs& a, int precision, int grid, hipStream_t s);
 // Coefficient-bin sums -> knot gradients.  out[r][f][k] += w[r] dU_r/dtheta_{f,k}
-// (per replica), or out[f][k] += sum_r w[r] dU_r/dtheta_{f,k} when reduce;
-// scratch: device doubles, >= 3 * 3 * nmax per output row.
-int launch_adjoint_finish(const AdjointArgs& a, const double* w, int reduce, double* out, double* scratch,
-                          hipStream_t s);
+// (per replica), or out[f][k] += sum_r w[r] dU_r/dtheta_{f,k} when reduce
+// (which overwrites replica 0's bins).
+int launch_adjoint_finish(const AdjointArgs& a, const double* w, int reduce, double* out, hipStream_t s);
 // Rows in [N][out_cap] row-major order (slots past the row length = -1).
 int launch_rows_rowmajor(const int32_t* nbr, const int32_t* nnb, int N, int cap, int32_t* out, int out_cap,
                          hipStream_t s);

@@ -2368,63 +2368,109 @@ __global__ __launch_bounds__(kAdjBlock) void k_adjoint(AdjointArgs a)
     if (rep >= 0) flush();
 }
 
-// One thread per (output row, function): fixed-point bins -> coefficient
-// gradients g = (g_a, g_b, g_c, d_d) per interval -> knot gradient through the
-// transpose of the natural-spline map.  With y the knots and M the second
-// derivatives (M_0 = M_{n-1} = 0, K M = r, K = tridiag(1, 4, 1),
-// r_l = 6 (y_{l+1} - 2 y_l + y_{l-1}) / h^2):
+// Reduction over the replicas: each thread owns one coefficient bin of one
+// function and adds w[r] times its fixed-point sums in replica order, every
+// load independent of the adds.  The double takes the place of replica 0's
+// bin (scratch of this call), which no other thread reads.
+__global__ void k_adjoint_sum(unsigned long long* bins, size_t stride, int n_rep, const double* w)
+{
+    const size_t k = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= stride) return;
+    double s = 0.0;
+#pragma unroll 8
+    for (int r = 0; r < n_rep; ++r)
+        s += (w ? w[r] : 1.0) * ((double)(long long)bins[(size_t)r * stride + k] * kFixInv);
+    ((double*)bins)[k] = s;
+}
+
+// Coefficient bins -> knot gradient, one block per (output row, function):
+// coefficient gradients g = (g_a, g_b, g_c, g_d) per interval -> knot
+// gradient through the transpose of the natural-spline map.  With y the knots
+// and M the second derivatives (M_0 = M_{n-1} = 0, K M = r, K = tridiag(1, 4,
+// 1), r_l = 6 (y_{l+1} - 2 y_l + y_{l-1}) / h^2):
 //   a_m = y_m, b_m = y_{m+1} - y_m - h^2 (2 M_m + M_{m+1})/6,
 //   c_m = h^2 M_m / 2, d_m = h^2 (M_{m+1} - M_m)/6,
 // so dU/dy = direct terms + (dr/dy)^T K^{-1} (dU/dM).
-__global__ void k_adjoint_finish(AdjointArgs a, const double* w, int reduce, double* out, double* scratch)
+// K is solved by the two Thomas recurrences.  Both forget their start by a
+// factor 2 - sqrt 3 = 0.268 per knot, so each thread takes a run of knots and
+// starts kWarm knots ahead of it: what it leaves out is 0.268^48 = 4e-28 of
+// the entries there, far below float64 rounding.  A serial solve by one
+// thread took 5 to 10 ms at 2000 knots (a division and several dependent
+// loads per knot); this takes a few microseconds.
+constexpr int kFinBlock = 256;
+constexpr int kWarm = 48;
+constexpr int kPivots = 24;   // the pivots 4, 4 - 1/4, ... are 2 + sqrt 3 to float64 from here on
+
+template <bool kSummed>
+__global__ __launch_bounds__(kFinBlock) void k_adjoint_finish(AdjointArgs a, const double* w, double* out)
 {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    const int rows = reduce ? 1 : a.n_rep;
-    if (t >= rows * 3) return;
-    const int row = t / 3, f = t % 3;
+    extern __shared__ double fin_lds[];
+    __shared__ double rpiv[kPivots + 1];   // 1 / pivot of interior knot k (k >= 1)
+    const int row = blockIdx.x / 3, f = blockIdx.x % 3;
     const int n = f == 2 ? a.tab.n_rho : a.tab.n_r;
     const double h = f == 2 ? 1.0 / a.tab.inv_h_rho : 1.0 / a.tab.inv_h_r;
     const int nmax = a.nb + 1;
-    double* gM = scratch + (size_t)t * 2 * nmax;
-    double* dg = gM + nmax;
+    double* gM = fin_lds;           // dU/dM, then the solution z
+    double* y = fin_lds + nmax;     // after the forward recurrence
     double* o = out + ((size_t)row * 3 + f) * nmax;
-    const int r0 = reduce ? 0 : row, r1 = reduce ? a.n_rep : row + 1;
-    auto g = [&](int m, int q) {   // coefficient gradient, fixed replica order
-        double s = 0.0;
-        for (int r = r0; r < r1; ++r) {
-            const long long v = (long long)a.bins[(((size_t)r * 3 + f) * a.nb + m) * 4 + q];
-            s += (w ? w[r] : 1.0) * ((double)v * kFixInv);
-        }
-        return s;
+    const unsigned long long* bins = a.bins + ((size_t)(kSummed ? 0 : row) * 3 + f) * (size_t)a.nb * 4;
+    const double wr = !kSummed && w ? w[row] : 1.0;
+    auto g = [&](int m, int q) {
+        if constexpr (kSummed) return __longlong_as_double((long long)bins[4 * (size_t)m + q]);
+        else return wr * ((double)(long long)bins[4 * (size_t)m + q] * kFixInv);
     };
     const double h2 = h * h;
-    // dU/dM for interior knots, and the direct y terms
-    for (int k = 0; k < n; ++k) {
-        double dy = 0.0, gm = 0.0;
-        if (k <= n - 2) dy += g(k, 0) - g(k, 1);
-        if (k >= 1) dy += g(k - 1, 1);
+    if (threadIdx.x == 0) {
+        double d = 4.0;
+        for (int k = 1; k <= kPivots; ++k) {
+            rpiv[k] = 1.0 / d;
+            d = 4.0 - rpiv[k];
+        }
+    }
+    auto rp = [&](int k) { return rpiv[min(k, kPivots)]; };
+    // dU/dM of the interior knots (0 at the ends)
+    for (int k = threadIdx.x; k < n; k += kFinBlock) {
+        double gm = 0.0;
         if (k >= 1 && k <= n - 2)
             gm = h2 / 6.0 * (-2.0 * g(k, 1) - g(k - 1, 1) + 3.0 * g(k, 2) - g(k, 3) + g(k - 1, 3));
-        o[k] += dy;
         gM[k] = gm;
     }
-    // solve K z = gM on the interior (Thomas); z overwrites gM
-    dg[1] = 4.0;
-    for (int k = 2; k <= n - 2; ++k) {
-        const double q = 1.0 / dg[k - 1];
-        dg[k] = 4.0 - q;
-        gM[k] -= q * gM[k - 1];
+    __syncthreads();
+    // this thread's interior knots k0 .. k1 - 1
+    const int per = (n - 2 + kFinBlock - 1) / kFinBlock;
+    const int k0 = 1 + (int)threadIdx.x * per, k1 = min(n - 1, k0 + per);
+    if (k0 < k1) {
+        int k = max(1, k0 - kWarm);
+        double v = gM[k];
+        if (k >= k0) y[k] = v;
+        for (++k; k < k1; ++k) {
+            v = gM[k] - rp(k - 1) * v;
+            if (k >= k0) y[k] = v;
+        }
     }
-    gM[n - 2] /= dg[n - 2];
-    for (int k = n - 3; k >= 1; --k) gM[k] = (gM[k] - gM[k + 1]) / dg[k];
-    gM[0] = 0.0;
-    gM[n - 1] = 0.0;
+    __syncthreads();
+    if (k0 < k1) {
+        int k = min(n - 2, k1 - 1 + kWarm);
+        double z = y[k] * rp(k);
+        if (k < k1) gM[k] = z;
+        for (--k; k >= k0; --k) {
+            z = (y[k] - z) * rp(k);
+            if (k < k1) gM[k] = z;
+        }
+    }
+    __syncthreads();
     const double s6 = 6.0 / h2;
-    for (int k = 0; k < n; ++k) {
-        double v = -2.0 * gM[k];
-        if (k >= 1) v += gM[k - 1];
-        if (k + 1 <= n - 1) v += gM[k + 1];
-        o[k] += s6 * v;
+    for (int k = threadIdx.x; k < n; k += kFinBlock) {
+        double dy = 0.0, v = -2.0 * gM[k];   // gM is zero at both ends
+        if (k <= n - 2) {
+            dy += g(k, 0) - g(k, 1);
+            v += gM[k + 1];
+        }
+        if (k >= 1) {
+            dy += g(k - 1, 1);
+            v += gM[k - 1];
+        }
+        o[k] += dy + s6 * v;
     }
 }
 
@@ -2444,11 +2490,20 @@ int launch_adjoint(const AdjointArgs& a, int precision, int grid, hipStream_t s)
     return precision ? launch_adjoint_t<float>(a, grid, s) : launch_adjoint_t<double>(a, grid, s);
 }
 
-int launch_adjoint_finish(const AdjointArgs& a, const double* w, int reduce, double* out, double* scratch,
-                          hipStream_t s)
+int launch_adjoint_finish(const AdjointArgs& a, const double* w, int reduce, double* out, hipStream_t s)
 {
-    const int threads = (reduce ? 1 : a.n_rep) * 3;
-    hipLaunchKernelGGL(k_adjoint_finish, dim3((threads + 63) / 64), dim3(64), 0, s, a, w, reduce, out, scratch);
+    const size_t lds = 2 * (size_t)(a.nb + 1) * sizeof(double);
+    const int rows = reduce ? 1 : a.n_rep;
+    if (reduce) {
+        const size_t stride = (size_t)3 * a.nb * 4;
+        hipLaunchKernelGGL(k_adjoint_sum, dim3((unsigned)((stride + 255) / 256)), dim3(256), 0, s, a.bins, stride,
+                           a.n_rep, w);
+        allow_lds(reinterpret_cast<const void*>(&k_adjoint_finish<true>), lds);
+        hipLaunchKernelGGL(k_adjoint_finish<true>, dim3(3 * rows), dim3(kFinBlock), lds, s, a, w, out);
+    } else {
+        allow_lds(reinterpret_cast<const void*>(&k_adjoint_finish<false>), lds);
+        hipLaunchKernelGGL(k_adjoint_finish<false>, dim3(3 * rows), dim3(kFinBlock), lds, s, a, w, out);
+    }
     return (int)hipGetLastError();
 }
 

@@ -69,6 +69,38 @@ def test_adjoint_identities_and_reduction(knots):
     ctx.close()
 
 
+# the knot transform is solved by runs of knots per thread (256 threads, 48
+# knots of lead-in): fewer interior knots than threads, one and two interior
+# knots, a run's edge, the lead-in's, and the largest table.  Tolerance: the
+# bins hold each evaluation to 2^-33, as in the test against the oracle above
+@pytest.mark.parametrize("n", [3, 4, 50, 257, 258, 259, 2561, 2562, 5121])
+def test_adjoint_knot_counts(oracle_lib, n):
+    import torch
+
+    import paper_2201_04622_amd.eamfe as E
+    reps = _batch()
+    r = np.linspace(0.0, 1.0, n)
+    rho = np.linspace(0.0, 200.0, n)
+    knots = I.PotentialKnots(I.R_CUT, 200.0, 0.3 * (1.0 - r) ** 2 * (1.0 - 2.0 * r), 4.0 * (1.0 - r) ** 3,
+                             -np.sqrt(1.0 + rho))
+    opot = oracle_lib.Potential.from_knots(knots)
+    ctx, x0, arrs = make_ctx(reps, FP64, 2, 256, knots=knots)
+    x = I.displaced(arrs["x0"], 0.07, seed=31)
+    g = torch.zeros(len(reps), 3, n, dtype=torch.float64, device="cuda")
+    ctx.adjoint_theta(E.to_soa(x), g)
+    red = torch.zeros(3, n, dtype=torch.float64, device="cuda")
+    w = np.array([0.5, -2.0, 3.0])
+    ctx.adjoint_theta(E.to_soa(x), red, weights=w, reduce=True)
+    gg = g.cpu().numpy()
+    say(f"adjoint, {n} knots")
+    for q, (rep, xr) in enumerate(zip(reps, split(x, ctx.offsets))):
+        ref = opot.adjoint_theta(xr, rep.box)
+        for f in range(3):
+            assert np.linalg.norm(gg[q, f] - ref[f]) < 1e-9 * np.linalg.norm(ref[f]), (q, f)
+    assert np.allclose(red.cpu().numpy(), np.tensordot(w, gg, axes=1), rtol=1e-12, atol=1e-9)
+    ctx.close()
+
+
 def test_adjoint_matches_gpu_energy_differences(knots):
     import torch
 
