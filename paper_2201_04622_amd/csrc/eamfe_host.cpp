@@ -936,10 +936,7 @@ int adjoint_at(eamfe_ctx* c, const double4* P, const double* w_host, int reduce,
     a.tab = tables_of(c);
     a.N = c->N;
     a.n_rep = c->n_rep;
-    a.tile_atoms = 64 / c->lanes;
-    a.n_units = c->n_tiles;
-    const int grid = std::max(1, std::min(c->n_tiles, 2 * c->n_cu));
-    LCHK(c, launch_adjoint(a, c->precision, grid, c->stream));
+    LCHK(c, launch_adjoint(a, c->precision, c->n_cu, c->stream));
     LCHK(c, launch_adjoint_finish(a, wd, reduce, out, c->stream));
     return EAMFE_OK;
 }

@@ -178,8 +178,7 @@ struct AdjointArgs {
     Tables tab;
     int N;
     int n_rep;
-    int tile_atoms;             // atoms per work unit
-    int n_units;                // total work units (replica-major)
+    int lanes;                  // lanes per atom (set by the launcher)
 };
 
 // LDS of one block of the LDS row builder (k_rows_lds): the records and
@@ -221,7 +220,7 @@ int launch_advance_iter(int64_t* iter, int64_t by, hipStream_t s);
 int launch_init_velocities(const StepArgs& a, int n_rep, int fix_com, hipStream_t s);
 // per-replica mean-squared displacement from x0 with the centre of mass removed -> out[n_rep] (device)
 int launch_msd(const double* x, const double* x0, const RepDesc* reps, int n_rep, int N, double* out, hipStream_t s);
-int launch_adjoint(const AdjointArgs& a, int precision, int grid, hipStream_t s);
+int launch_adjoint(const AdjointArgs& a, int precision, int n_cu, hipStream_t s);
 // Coefficient-bin sums -> knot gradients.  out[r][f][k] += w[r] dU_r/dtheta_{f,k}
 // (per replica), or out[f][k] += sum_r w[r] dU_r/dtheta_{f,k} when reduce
 // (which overwrites replica 0's bins).

@@ -2266,106 +2266,138 @@ int launch_init_velocities(const StepArgs& a, int n_rep, int fix_com, hipStream_
 // Knot gradient dU/dtheta (theta = knot values of phi, rho, F).
 // U is linear in the interval coefficients of phi and F, and rho_i is linear
 // in those of rho, so with B(t) = (1, t, t^2, t^3) of every evaluation:
-//   dU/dc_phi[m] = 1/2 sum over ordered pairs in interval m of B
-//   dU/dc_rho[m] = sum_i F'(rho_i) sum_j over pairs in interval m of B
+//   dU/dc_phi[m] = sum over pairs i < j in interval m of B
+//   dU/dc_rho[m] = sum over pairs i < j in interval m of (F'(rho_i) + F'(rho_j)) B
 //   dU/dc_F[m]   = sum over atoms with rho_i in interval m of B
-// Each block accumulates one function's bins in an LDS histogram (2^-32
-// fixed point, 64-bit) over a contiguous range of work units and adds it to
-// the replica's global bins when the replica changes.
+// A block takes an equal share of the atoms, one replica after another, and
+// accumulates the bins of phi and of rho in LDS histograms (2^-32 fixed point,
+// 64-bit) that it adds to the replica's global bins when the replica changes.
+// Both functions in one pass: the separation, its root and the interval are
+// evaluated once and the rows and records are read once (64 bytes of LDS per
+// interval, so up to 2561 knots on gfx950; larger tables take a pass each).
+// In the histogram the four powers sit in four arrays of nint entries: pairs
+// of a wavefront fall on random intervals and so on random banks, where
+// consecutive words per interval put every one of them on an eighth of the
+// banks.  The F bins take one atom each and go to the global bins directly.
+// Bound by the latency of slab, record and root per turn (about three turns
+// per lane) and then by the LDS atomics (12 cycles per wavefront).  16
+// replicas, 25,560 atoms, rows of 180, FP32: 44 us, of them 7 us for adding
+// the histograms to the global bins (74 us with words of one power, so of
+// different cache lines, in consecutive threads); 148 us as one kernel per
+// function over ordered pairs.
 // --------------------------------------------------------------------------
-constexpr int kAdjBlock = 256;
-constexpr int kAdjLanes = 8;
+constexpr int kAdjBlock = 1024;
+constexpr int kAdjAtoms = 64;   // atoms per block at least, or the flush of its histograms outweighs the pairs
 
 __device__ __forceinline__ unsigned long long fix64(double v)
 {
     return (unsigned long long)__double2ll_rn(v * kFixScale);
 }
 
-template <typename real, int WHICH>
+template <typename real, bool kPhi, bool kRho>
 __global__ __launch_bounds__(kAdjBlock) void k_adjoint(AdjointArgs a)
 {
     extern __shared__ unsigned long long hist[];
     constexpr bool kQ = sizeof(real) == 4;
-    const int nint = (WHICH == 2 ? a.tab.n_rho : a.tab.n_r) - 1;
-    for (int k = threadIdx.x; k < 4 * nint; k += blockDim.x) hist[k] = 0ull;
+    const int nint = a.tab.n_r - 1;
+    const int words = ((kPhi ? 4 : 0) + (kRho ? 4 : 0)) * nint;
+    unsigned long long* const hp = hist;                              // phi: [4][nint]
+    unsigned long long* const hr = hist + (kPhi ? 4 * nint : 0);      // rho: [4][nint]
+    for (int k = threadIdx.x; k < words; k += blockDim.x) hist[k] = 0ull;
     __syncthreads();
-    const int per = (a.n_units + gridDim.x - 1) / gridDim.x;
-    const int u0 = blockIdx.x * per, u1 = min(a.n_units, u0 + per);
-    int rep = -1;
-    auto flush = [&]() {
-        __syncthreads();
-        unsigned long long* g = a.bins + ((size_t)rep * 3 + WHICH) * (size_t)a.nb * 4;
-        for (int k = threadIdx.x; k < 4 * nint; k += blockDim.x) {
-            const unsigned long long v = hist[k];
-            if (v) {
-                atomicAdd(&g[k], v);
-                hist[k] = 0ull;
-            }
-        }
-        __syncthreads();
-    };
-    const int A = a.tile_atoms;
-    const int lane = threadIdx.x % kAdjLanes;
-    const int slot = threadIdx.x / kAdjLanes;
-    constexpr int per_pass = kAdjBlock / kAdjLanes;
-    for (int u = u0; u < u1; ++u) {
-        int r = rep < 0 ? 0 : rep;   // replica of unit u (units are replica-major)
-        while (u >= a.reps[r].tile_base + a.reps[r].n_tiles) ++r;
-        if (r != rep) {
-            if (rep >= 0) flush();
-            rep = r;
-        }
+    const int i0 = (int)((long long)a.N * blockIdx.x / gridDim.x);
+    const int i1 = (int)((long long)a.N * (blockIdx.x + 1) / gridDim.x);
+    const int T = a.lanes, lane = threadIdx.x % T, slot = threadIdx.x / T, slots = blockDim.x / T;
+    int r = 0;   // replica of atom i0: the last with off <= i0
+    for (int hi = a.n_rep; hi - r > 1;) {
+        const int mid = (r + hi) >> 1;
+        if (a.reps[mid].off <= i0) r = mid;
+        else hi = mid;
+    }
+    for (int first = i0; first < i1; ++r) {
         const RepDesc& R = a.reps[r];
-        const int first = R.off + (u - R.tile_base) * A;
-        const int count = min(A, R.n - (u - R.tile_base) * A);
-        for (int c0 = 0; c0 < count; c0 += per_pass) {
-            const int la = c0 + slot;
-            if (la >= count) continue;
-            const int i = first + la;
-            if constexpr (WHICH == 2) {
-                if (lane == 0) {
-                    double td;
-                    const int m = interval<double>(a.rho[i], a.tab.inv_h_rho, a.tab.n_rho, td);
-                    atomicAdd(&hist[4 * m + 0], fix64(1.0));
-                    atomicAdd(&hist[4 * m + 1], fix64(td));
-                    atomicAdd(&hist[4 * m + 2], fix64(td * td));
-                    atomicAdd(&hist[4 * m + 3], fix64(td * td * td));
-                }
-            } else {
-                const double4 pi = a.P[i];
-                const uint4 qi = kQ ? a.Q[i] : make_uint4(0u, 0u, 0u, 0u);
-                const double wgt = WHICH == 0 ? 0.5 : (kQ ? (double)__uint_as_float(qi.w) : pi.w);
-                const int n = a.nnb[i];
-                for (int q = lane; q < n; q += kAdjLanes) {
-                    // geometry in float64 in both forms: the basis weights B(t) vary on the
-                    // scale of one interval, so t needs more than single precision
-                    const int j = a.nbr[slot_index(i, q, a.N)];
+        const int end = min(i1, R.off + R.n);
+        const double sx = R.L[0] * 2.3283064365386963e-10, sy = R.L[1] * 2.3283064365386963e-10,
+                     sz = R.L[2] * 2.3283064365386963e-10;
+        unsigned long long* const g = a.bins + (size_t)r * 3 * (size_t)a.nb * 4;
+        for (int i = first + slot; i < end; i += slots) {
+            const int n = a.nnb[i];
+            const double4 pi = a.P[i];
+            const uint4 qi = kQ ? a.Q[i] : make_uint4(0u, 0u, 0u, 0u);
+            const double wi = kQ ? (double)__uint_as_float(qi.w) : pi.w;
+            if (kRho && lane < 4) {   // the atom's F bins, a power per lane
+                double td;
+                const int m = interval<double>(a.rho[i], a.tab.inv_h_rho, a.tab.n_rho, td);
+                const double b = lane == 0 ? 1.0 : lane == 1 ? td : lane == 2 ? td * td : td * td * td;
+                atomicAdd(&g[((size_t)2 * a.nb + m) * 4 + lane], fix64(b));
+            }
+            for (int b = 4 * lane; b < n; b += 4 * T) {   // one slab of four neighbours per turn
+                const int4 js = row_slab(a.nbr, i, b, a.N);
+                const int j[4] = {js.x, js.y, js.z, js.w};
+                // geometry in float64 in both forms: the basis weights B(t) vary on the
+                // scale of one interval, so t needs more than single precision
+                double r2[4], wr[4];
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
                     double dx, dy, dz;
                     if constexpr (kQ) {
-                        const uint4 qj = a.Q[j];
-                        dx = (double)(int)(qi.x - qj.x) * (R.L[0] * 2.3283064365386963e-10);
-                        dy = (double)(int)(qi.y - qj.y) * (R.L[1] * 2.3283064365386963e-10);
-                        dz = (double)(int)(qi.z - qj.z) * (R.L[2] * 2.3283064365386963e-10);
+                        const uint4 qj = a.Q[j[s]];
+                        wr[s] = wi + (double)__uint_as_float(qj.w);
+                        dx = (double)(int)(qi.x - qj.x) * sx;
+                        dy = (double)(int)(qi.y - qj.y) * sy;
+                        dz = (double)(int)(qi.z - qj.z) * sz;
                     } else {
-                        const double3 d = sep(R, pi, a.P[j]);
+                        const double4 pj = a.P[j[s]];
+                        wr[s] = wi + pj.w;
+                        const double3 d = sep(R, pi, pj);
                         dx = d.x;
                         dy = d.y;
                         dz = d.z;
                     }
-                    const double r2 = dx * dx + dy * dy + dz * dz;
-                    if (r2 < a.tab.rc2) {
-                        double td;
-                        const int m = interval<double>(sqrt(r2), a.tab.inv_h_r, a.tab.n_r, td);
-                        atomicAdd(&hist[4 * m + 0], fix64(wgt));
-                        atomicAdd(&hist[4 * m + 1], fix64(wgt * td));
-                        atomicAdd(&hist[4 * m + 2], fix64(wgt * td * td));
-                        atomicAdd(&hist[4 * m + 3], fix64(wgt * td * td * td));
+                    r2[s] = dx * dx + dy * dy + dz * dz;
+                }
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    // each pair once (the padding of a row's last slab is i itself)
+                    if (j[s] <= i || !(r2[s] < a.tab.rc2)) continue;
+                    double td;
+                    const int m = interval<double>(sqrt(r2[s]), a.tab.inv_h_r, a.tab.n_r, td);
+                    if constexpr (kPhi) {
+                        atomicAdd(&hp[m], fix64(1.0));
+                        atomicAdd(&hp[nint + m], fix64(td));
+                        atomicAdd(&hp[2 * nint + m], fix64(td * td));
+                        atomicAdd(&hp[3 * nint + m], fix64(td * td * td));
+                    }
+                    if constexpr (kRho) {
+                        atomicAdd(&hr[m], fix64(wr[s]));
+                        atomicAdd(&hr[nint + m], fix64(wr[s] * td));
+                        atomicAdd(&hr[2 * nint + m], fix64(wr[s] * td * td));
+                        atomicAdd(&hr[3 * nint + m], fix64(wr[s] * td * td * td));
                     }
                 }
             }
         }
+        // the replica's share of this block is done: into its global bins,
+        // consecutive threads to consecutive words (a function's [nint][4]):
+        // the atomics cost by the cache line, not by the word
+        __syncthreads();
+#pragma unroll
+        for (int f = 0; f < 2; ++f) {
+            if (!(f ? kRho : kPhi)) continue;
+            unsigned long long* const hf = f ? hr : hp;
+            unsigned long long* const gf = g + (size_t)f * a.nb * 4;
+            for (int k = threadIdx.x; k < 4 * nint; k += blockDim.x) {
+                const int at = (k & 3) * nint + (k >> 2);
+                const unsigned long long v = hf[at];
+                if (v) {
+                    atomicAdd(&gf[k], v);
+                    hf[at] = 0ull;
+                }
+            }
+        }
+        __syncthreads();
+        first = end;
     }
-    if (rep >= 0) flush();
 }
 
 // Reduction over the replicas: each thread owns one coefficient bin of one
@@ -2393,13 +2425,31 @@ __global__ void k_adjoint_sum(unsigned long long* bins, size_t stride, int n_rep
 // so dU/dy = direct terms + (dr/dy)^T K^{-1} (dU/dM).
 // K is solved by the two Thomas recurrences.  Both forget their start by a
 // factor 2 - sqrt 3 = 0.268 per knot, so each thread takes a run of knots and
-// starts kWarm knots ahead of it: what it leaves out is 0.268^48 = 4e-28 of
-// the entries there, far below float64 rounding.  A serial solve by one
-// thread took 5 to 10 ms at 2000 knots (a division and several dependent
-// loads per knot); this takes a few microseconds.
-constexpr int kFinBlock = 256;
-constexpr int kWarm = 48;
+// starts kWarm knots ahead of it: what it leaves out is 0.268^32 = 5e-19 of
+// the entries there, below float64 rounding.  Bound by latency: one round of
+// global reads (every read of the thread issued together), then two chains of
+// kWarm multiply-adds out of LDS.  At 2000 knots a serial solve by one thread
+// per row took 5.1 ms (16 replicas) and 9.9 ms (4 replicas summed); this
+// takes 9.4 and 8.3 us.
+constexpr int kFinBlock = 1024;
+constexpr int kFinPer = 6;    // knots per thread: at most 6144 (the histograms stop at 5121)
+constexpr int kWarm = 32;
 constexpr int kPivots = 24;   // the pivots 4, 4 - 1/4, ... are 2 + sqrt 3 to float64 from here on
+
+struct PivotTable {
+    double r[kPivots + 1];    // 1 / pivot of interior knot k
+};
+constexpr PivotTable pivots()
+{
+    PivotTable t{};
+    double d = 4.0;
+    for (int k = 1; k <= kPivots; ++k) {
+        t.r[k] = 1.0 / d;
+        d = 4.0 - t.r[k];
+    }
+    return t;
+}
+__constant__ const PivotTable kRecip = pivots();
 
 template <bool kSummed>
 __global__ __launch_bounds__(kFinBlock) void k_adjoint_finish(AdjointArgs a, const double* w, double* out)
@@ -2415,79 +2465,115 @@ __global__ __launch_bounds__(kFinBlock) void k_adjoint_finish(AdjointArgs a, con
     double* o = out + ((size_t)row * 3 + f) * nmax;
     const unsigned long long* bins = a.bins + ((size_t)(kSummed ? 0 : row) * 3 + f) * (size_t)a.nb * 4;
     const double wr = !kSummed && w ? w[row] : 1.0;
-    auto g = [&](int m, int q) {
-        if constexpr (kSummed) return __longlong_as_double((long long)bins[4 * (size_t)m + q]);
-        else return wr * ((double)(long long)bins[4 * (size_t)m + q] * kFixInv);
+    auto val = [&](unsigned long long v) {
+        if constexpr (kSummed) return __longlong_as_double((long long)v);
+        else return wr * ((double)(long long)v * kFixInv);
     };
     const double h2 = h * h;
-    if (threadIdx.x == 0) {
-        double d = 4.0;
-        for (int k = 1; k <= kPivots; ++k) {
-            rpiv[k] = 1.0 / d;
-            d = 4.0 - rpiv[k];
+    // every global read at once: the thread's intervals m = threadIdx + u kFinBlock
+    // and the outputs at the same knots
+    ulonglong2 lo[kFinPer], hi[kFinPer];
+    double o0[kFinPer];
+#pragma unroll
+    for (int u = 0; u < kFinPer; ++u) {
+        const int m = (int)threadIdx.x + u * kFinBlock;
+        lo[u] = hi[u] = make_ulonglong2(0ull, 0ull);   // (as a double, and as an integer: 0)
+        o0[u] = 0.0;
+        if (m < n) o0[u] = o[m];
+        if (m < n - 1) {
+            lo[u] = ((const ulonglong2*)bins)[2 * m];
+            hi[u] = ((const ulonglong2*)bins)[2 * m + 1];
         }
     }
-    auto rp = [&](int k) { return rpiv[min(k, kPivots)]; };
-    // dU/dM of the interior knots (0 at the ends)
-    for (int k = threadIdx.x; k < n; k += kFinBlock) {
-        double gm = 0.0;
-        if (k >= 1 && k <= n - 2)
-            gm = h2 / 6.0 * (-2.0 * g(k, 1) - g(k - 1, 1) + 3.0 * g(k, 2) - g(k, 3) + g(k - 1, 3));
-        gM[k] = gm;
+    if (threadIdx.x <= kPivots) rpiv[threadIdx.x] = kRecip.r[threadIdx.x];
+    // interval k - 1's g_b and g_d reach knot k through LDS
+#pragma unroll
+    for (int u = 0; u < kFinPer; ++u) {
+        const int m = (int)threadIdx.x + u * kFinBlock;
+        if (m < n) {
+            y[m] = val(lo[u].y);
+            gM[m] = val(hi[u].y);
+        }
     }
     __syncthreads();
-    // this thread's interior knots k0 .. k1 - 1
+    double dy[kFinPer], gm[kFinPer];   // direct terms, and dU/dM of the interior knots (0 at the ends)
+#pragma unroll
+    for (int u = 0; u < kFinPer; ++u) {
+        const int k = (int)threadIdx.x + u * kFinBlock;
+        const double ga = val(lo[u].x), gb = val(lo[u].y), gc = val(hi[u].x), gd = val(hi[u].y);
+        const double gb1 = k >= 1 && k < n ? y[k - 1] : 0.0, gd1 = k >= 1 && k < n ? gM[k - 1] : 0.0;
+        dy[u] = ga - gb + gb1;
+        gm[u] = k >= 1 && k <= n - 2 ? h2 / 6.0 * (-2.0 * gb - gb1 + 3.0 * gc - gd + gd1) : 0.0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kFinPer; ++u) {
+        const int k = (int)threadIdx.x + u * kFinBlock;
+        if (k < n) gM[k] = gm[u];
+    }
+    __syncthreads();
+    auto rp = [&](int k) { return rpiv[max(1, min(k, kPivots))]; };
+    // this thread's interior knots k0 .. k1 - 1, after a lead-in of kWarm
+    // (entries 0 of gM and n - 1 of y are zero, so a lead-in that starts
+    // before the first or after the last interior knot adds nothing)
     const int per = (n - 2 + kFinBlock - 1) / kFinBlock;
     const int k0 = 1 + (int)threadIdx.x * per, k1 = min(n - 1, k0 + per);
     if (k0 < k1) {
-        int k = max(1, k0 - kWarm);
-        double v = gM[k];
-        if (k >= k0) y[k] = v;
-        for (++k; k < k1; ++k) {
+        double v = 0.0;
+#pragma unroll 8
+        for (int q = kWarm; q > 0; --q) v = gM[max(k0 - q, 0)] - rp(k0 - q - 1) * v;
+        for (int k = k0; k < k1; ++k) {
             v = gM[k] - rp(k - 1) * v;
-            if (k >= k0) y[k] = v;
+            y[k] = v;
         }
     }
+    if (threadIdx.x == 0) y[n - 1] = 0.0;
     __syncthreads();
     if (k0 < k1) {
-        int k = min(n - 2, k1 - 1 + kWarm);
-        double z = y[k] * rp(k);
-        if (k < k1) gM[k] = z;
-        for (--k; k >= k0; --k) {
+        double z = 0.0;
+#pragma unroll 8
+        for (int q = kWarm; q > 0; --q) z = (y[min(k1 - 1 + q, n - 1)] - z) * rp(k1 - 1 + q);
+        for (int k = k1 - 1; k >= k0; --k) {
             z = (y[k] - z) * rp(k);
-            if (k < k1) gM[k] = z;
+            gM[k] = z;
         }
     }
     __syncthreads();
     const double s6 = 6.0 / h2;
-    for (int k = threadIdx.x; k < n; k += kFinBlock) {
-        double dy = 0.0, v = -2.0 * gM[k];   // gM is zero at both ends
-        if (k <= n - 2) {
-            dy += g(k, 0) - g(k, 1);
-            v += gM[k + 1];
+#pragma unroll
+    for (int u = 0; u < kFinPer; ++u) {
+        const int k = (int)threadIdx.x + u * kFinBlock;
+        if (k < n) {   // gM is zero at both ends
+            const double v = (k >= 1 ? gM[k - 1] : 0.0) - 2.0 * gM[k] + (k <= n - 2 ? gM[k + 1] : 0.0);
+            o[k] = o0[u] + (dy[u] + s6 * v);
         }
-        if (k >= 1) {
-            dy += g(k - 1, 1);
-            v += gM[k - 1];
-        }
-        o[k] += dy + s6 * v;
     }
 }
 
 template <typename real>
-static int launch_adjoint_t(const AdjointArgs& a, int grid, hipStream_t s)
+static int launch_adjoint_t(AdjointArgs a, int n_cu, hipStream_t s)
 {
-    const size_t sh_r = (size_t)(a.tab.n_r - 1) * 4 * sizeof(unsigned long long);
-    const size_t sh_f = (size_t)(a.tab.n_rho - 1) * 4 * sizeof(unsigned long long);
-    hipLaunchKernelGGL((k_adjoint<real, 0>), dim3(grid), dim3(kAdjBlock), sh_r, s, a);
-    hipLaunchKernelGGL((k_adjoint<real, 1>), dim3(grid), dim3(kAdjBlock), sh_r, s, a);
-    hipLaunchKernelGGL((k_adjoint<real, 2>), dim3(grid), dim3(kAdjBlock), sh_f, s, a);
+    const int grid = std::max(1, std::min(n_cu, (a.N + kAdjAtoms - 1) / kAdjAtoms));
+    // lanes per atom: enough for a block's atoms to occupy its threads, up to 32
+    const int atoms = (a.N + grid - 1) / grid;
+    a.lanes = 8;
+    while (a.lanes < 32 && 2 * a.lanes * atoms <= kAdjBlock) a.lanes *= 2;
+    const size_t one = (size_t)(a.tab.n_r - 1) * 4 * sizeof(unsigned long long);
+    if (2 * one <= device_lds()) {
+        allow_lds(reinterpret_cast<const void*>(&k_adjoint<real, true, true>), 2 * one);
+        hipLaunchKernelGGL((k_adjoint<real, true, true>), dim3(grid), dim3(kAdjBlock), 2 * one, s, a);
+    } else {
+        allow_lds(reinterpret_cast<const void*>(&k_adjoint<real, true, false>), one);
+        allow_lds(reinterpret_cast<const void*>(&k_adjoint<real, false, true>), one);
+        hipLaunchKernelGGL((k_adjoint<real, true, false>), dim3(grid), dim3(kAdjBlock), one, s, a);
+        hipLaunchKernelGGL((k_adjoint<real, false, true>), dim3(grid), dim3(kAdjBlock), one, s, a);
+    }
     return (int)hipGetLastError();
 }
 
-int launch_adjoint(const AdjointArgs& a, int precision, int grid, hipStream_t s)
+int launch_adjoint(const AdjointArgs& a, int precision, int n_cu, hipStream_t s)
 {
-    return precision ? launch_adjoint_t<float>(a, grid, s) : launch_adjoint_t<double>(a, grid, s);
+    return precision ? launch_adjoint_t<float>(a, n_cu, s) : launch_adjoint_t<double>(a, n_cu, s);
 }
 
 int launch_adjoint_finish(const AdjointArgs& a, const double* w, int reduce, double* out, hipStream_t s)

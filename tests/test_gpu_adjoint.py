@@ -69,11 +69,12 @@ def test_adjoint_identities_and_reduction(knots):
     ctx.close()
 
 
-# the knot transform is solved by runs of knots per thread (256 threads, 48
-# knots of lead-in): fewer interior knots than threads, one and two interior
-# knots, a run's edge, the lead-in's, and the largest table.  Tolerance: the
+# the knot transform is solved by runs of knots per thread (1024 threads, 32
+# knots of lead-in), the pair histograms hold both functions up to 2561 knots:
+# one and two interior knots, fewer interior knots than threads or than the
+# lead-in, a run's edge, both histogram forms, and the largest table.  Tolerance: the
 # bins hold each evaluation to 2^-33, as in the test against the oracle above
-@pytest.mark.parametrize("n", [3, 4, 50, 257, 258, 259, 2561, 2562, 5121])
+@pytest.mark.parametrize("n", [3, 4, 33, 259, 1025, 1026, 1027, 2561, 2562, 5121])
 def test_adjoint_knot_counts(oracle_lib, n):
     import torch
 
