@@ -585,7 +585,9 @@ NeighArgs neigh_args(eamfe_ctx* c, const double4* P)
     a.lds_atoms = c->lds_atoms;
     a.lds_cells = c->lds_cells;
     a.lds_waves = c->lds_waves;
-    a.lds_grid = c->n_cu;
+    // at least eight atoms per row-building block: below that the blocks' common
+    // work (flags, sort) is all they do
+    a.lds_grid = std::max(1, std::min(c->n_cu, (c->N + 7) / 8));
     return a;
 }
 

@@ -93,7 +93,7 @@ struct NeighArgs {
     int lds_atoms;              // the largest of them: atoms (records and sorted ids staged per block)
     int lds_cells;              // and cells (cell starts staged per block)
     int lds_waves;              // wavefronts per block of k_rows_lds
-    int lds_grid;               // row-building blocks of k_rows_lds (one more block finishes the force pass)
+    int lds_grid;               // blocks of k_rows_lds
     double rl2;                 // (r_cut + skin)^2
     float rl2_f;                // (r_cut + skin + margin)^2 for the single-precision candidate test
     double half_skin2;          // (skin/2)^2
@@ -181,22 +181,35 @@ struct AdjointArgs {
     int lanes;                  // lanes per atom (set by the launcher)
 };
 
-// LDS of one block of the LDS row builder (k_rows_lds): the records and
-// sorted ids of up to `atoms` atoms, `cells` + 1 cell starts, and per
-// wavefront a row buffer of `cap` slots.
+// LDS of the row builder: the sorted records of up to `atoms` atoms, then its
+// workspace: `cells` + 1 cell starts, the work entries (sorted position and
+// cell; at most one per cell plus two per wavefront) and per wavefront a row
+// buffer of `cap` slots and a chunk of the candidate stream (16-bit
+// positions).  The wavefronts' part also holds 16-bit ids of all atoms while
+// they are sorted (4 or more wavefronts of 2 KB and more).
 constexpr int kRowsAtomsMax = 4096;    // replicas of at most this many atoms (16-bit ids, 64 KB of records)
-constexpr int kRowsCellsMax = 4096;    // and at most this many cells use it
+constexpr int kRowsCellsMax = 4096;    // and at most this many cells use it (12 bits of a work entry)
+constexpr int kRowsStream = 1024;      // candidates per chunk
 
-__host__ __device__ inline size_t rows_lds_wave_bytes(int cap)
+struct RowsWs {
+    size_t cst, work, waves, wave;   // byte offsets; bytes per wavefront
+};
+
+__host__ __device__ inline RowsWs rows_ws(int cells, int cap)
 {
-    return (size_t)cap * 4;   // the row buffer
+    const auto up = [](size_t b) { return (b + 15) & ~(size_t)15; };
+    RowsWs r{};
+    r.cst = 0;
+    r.work = r.cst + up((size_t)(cells + 1) * 4);
+    r.waves = r.work + up((size_t)(cells + 32) * 4);
+    r.wave = (size_t)cap * 4 + kRowsStream * 2;
+    return r;
 }
 
 __host__ __device__ inline size_t rows_lds_bytes(int atoms, int cells, int cap, int waves)
 {
-    const size_t head = (size_t)atoms * 16 + (((size_t)atoms * 2 + 15) & ~(size_t)15) +
-                        (((size_t)(cells + 1) * 4 + 15) & ~(size_t)15);
-    return head + (size_t)waves * rows_lds_wave_bytes(cap);
+    const RowsWs r = rows_ws(cells, cap);
+    return (size_t)atoms * 16 + r.waves + (size_t)waves * r.wave;
 }
 
 // Launchers (eamfe_kernels.hip).  Each returns a hipError_t as int.

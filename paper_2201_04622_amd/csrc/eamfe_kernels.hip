@@ -28,6 +28,7 @@
 
 #include <hip/hip_ext.h>
 
+#include <type_traits>
 #include <vector>
 
 namespace eamfe {
@@ -228,7 +229,7 @@ __device__ __forceinline__ int4 row_slab(const int32_t* nbr, int i, int b0, int 
 // Records of one lane block's SB neighbours: box coordinates and F' bits
 // (FP32 form: record j - qoff of Q, a 32-bit byte offset from its base, with
 // Q the global array and qoff 0, or a replica's records staged in LDS and
-// qoff its first atom) or packed positions (FP64 form).
+// qoff its first atom) or packed positions (FP64 form, record j - qoff of P).
 template <bool kQ>
 struct Nb;
 template <>
@@ -248,7 +249,7 @@ __device__ __forceinline__ Nb<kQ> gather(const double4* P, const uint4* Q, int q
 #pragma unroll
     for (int s = 0; s < SB; ++s) {
         if constexpr (kQ) g.v[s] = *(const uint4*)((const char*)Q + (uint32_t)(js[s] - qoff) * 16u);
-        else g.v[s] = P[js[s]];
+        else g.v[s] = P[js[s] - qoff];
     }
     return g;
 }
@@ -987,31 +988,310 @@ __global__ __launch_bounds__(kListBlock) void k_list(NeighArgs a, int n_rep)
 }
 
 // --------------------------------------------------------------------------
-// Rows of replicas small enough for one block's LDS (k_rows_lds).  The grid
-// is one block per CU; every block reads the rebuild flags of
-// these replicas, splits the flagged ones into `parts` slices of atoms so
-// that the items fill the grid, and takes items in a fixed stride.  For its
-// item a block stages the replica's records in LDS, sorts its atoms into
-// the cells of the global builder (counting sort by cell, then each cell's
-// members by id) and builds the rows of the item's atoms from LDS alone: the
-// same candidate stream (stencil cells by offset, members by id) and the
-// same test as k_list, so the rows are identical to that builder's.
-// LDS: records [atoms], sorted ids [atoms] (16 bit), cell starts [cells + 1],
-// then per wavefront a row buffer [cap], the stencil's inclusive ends and
-// starts [2][128] and a candidate chunk [kRowsChunk] (16 bit).
+// Rows of replicas small enough for one block's LDS.  A block sorts the
+// replica's records by cell (the global builder's cells, each cell's members
+// by id) into LDS and builds the rows of its share of the atoms from LDS
+// alone: the same candidate stream (stencil cells by offset, members by id)
+// and the same test as k_list, so the rows are identical to that builder's.
+//
+// Atoms of one cell share their stencil, so a wavefront takes a cell (or a
+// share of its members, when a block has few atoms for its wavefronts): it
+// reads the stream's records into registers once, up to 16 per lane, and
+// tests every one of its atoms against them.  In the sorted order the five
+// cells of a stencil line along z are one run of records (two where they
+// wrap), so the stream is 25 runs, whose positions 50 lanes write out to LDS,
+// and its reads are nearly consecutive.  Bound by the tests' arithmetic (about
+// 24 instructions per 64 candidates and atom); with a wavefront per atom that
+// read all 125 cells' members anew the LDS reads bound it.  All 113,090 atoms
+// of the 64-replica batch: 197 -> 107 us; the two 2048-atom replicas of a
+// smaller run (16 atoms per block): 27 -> 19 us.
 // --------------------------------------------------------------------------
+constexpr int kCand = 16;              // candidates per lane held in registers
+static_assert(64 * kCand == kRowsStream, "one chunk of the stream fills the registers");
 
-__global__ __launch_bounds__(1024) void k_rows_lds(NeighArgs a, StepArgs s)
+// One chunk of a candidate stream, K per lane: box coordinates, and local ids
+// of 16 bits (0xffff past the stream's end).
+template <int K>
+struct RowsChunk {
+    static constexpr int n = K;
+    uint32_t x[K], y[K], z[K], id[K / 2];
+};
+
+// A replica's geometry for the builder.
+struct RowsGeom {
+    int nc0, nc1, nc2;       // cells per edge; nc0 == 0: all-pairs rows
+    float sx, sy, sz;        // box coordinate -> Angstrom
+    int roff, rn;            // first atom, atoms
+};
+
+__device__ __forceinline__ RowsGeom rows_geom(const RepDesc& R)
+{
+    return RowsGeom{R.nc[0], R.nc[1], R.nc[2], (float)(R.L[0] * 2.3283064365386963e-10),
+                    (float)(R.L[1] * 2.3283064365386963e-10), (float)(R.L[2] * 2.3283064365386963e-10), R.off, R.n};
+}
+
+// Rows of atoms [a0, a1) (local ids) of the replica g; record(k): box
+// coordinates of its atom k (global memory); st, ws: LDS for the sorted
+// records and rows_ws() of workspace.  The block has kRowsAtomsMax / kPer
+// threads, each of which holds up to kPer records.  Called by every thread of
+// the block; the caller has a barrier before st or ws are reused.
+template <int kPer, typename Rec>
+__device__ __forceinline__ void build_rows(const NeighArgs& a, const RowsGeom& g, Rec&& record, uint4* st, char* ws,
+                                           int a0, int a1)
+{
+    __shared__ int wsum[16];
+    __shared__ int sh_n, sh_next;
+    constexpr int bs = kRowsAtomsMax / kPer, nw = bs / 64;   // threads and wavefronts of the block
+    // (the empty asm keeps values of the thread's index out of the registers of
+    // a loop around this call)
+    int tid = threadIdx.x;
+    __asm__ volatile("" : "+v"(tid));
+    const int lw = tid & 63, w = tid >> 6;
+    const RowsWs lay = rows_ws(a.lds_cells, a.cap);
+    int* const cst = (int*)(ws + lay.cst);
+    uint32_t* const work = (uint32_t*)(ws + lay.work);
+    uint16_t* const tmp = (uint16_t*)(ws + lay.waves);   // members by cell in arrival order, before the rows
+    int* const row = (int*)(ws + lay.waves + (size_t)w * lay.wave);
+    uint16_t* const stream = (uint16_t*)(row + a.cap);
+    const uint16_t* const stream_l = stream + lw;
+    const int rn = g.rn, roff = g.roff, nc0 = g.nc0, nc1 = g.nc1, nc2 = g.nc2;
+    const int ncell = nc0 * nc1 * nc2;
+    // members per work entry: the cell's, but no more than an even share of
+    // the block's atoms per wavefront
+    const int share = max(1, (a1 - a0) / nw);
+    {
+        uint32_t qx[kPer], qy[kPer], qz[kPer], cs[kPer];   // records; cell and arrival index in it
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const uint4 q = record(min(tid + u * bs, rn - 1));
+            qx[u] = q.x;
+            qy[u] = q.y;
+            qz[u] = q.z;
+        }
+        for (int c = tid; c <= ncell; c += bs) cst[c] = 0;
+        if (tid == 0) sh_n = sh_next = 0;
+        __syncthreads();
+        if (nc0 > 0) {
+#pragma unroll
+            for (int u = 0; u < kPer; ++u)
+                if (tid + u * bs < rn) {
+                    const int c = (box_cell(qx[u], nc0) * nc1 + box_cell(qy[u], nc1)) * nc2 + box_cell(qz[u], nc2);
+                    cs[u] = (uint32_t)c | (uint32_t)atomicAdd(&cst[c], 1) << 12;
+                }
+            __syncthreads();
+            // counts -> starts: contiguous segments of cells per thread, then
+            // the segment totals across the block
+            const int per = (ncell + bs - 1) / bs;
+            const int c0 = tid * per, c1 = min(ncell, c0 + per);
+            int tot = 0;
+            for (int c = c0; c < c1; ++c) tot += cst[c];
+            const int incl = wave_scan(tot);
+            if (lw == 63) wsum[w] = incl;
+            __syncthreads();
+            int before = incl - tot;
+            for (int q = 0; q < w; ++q) before += wsum[q];
+            for (int c = c0; c < c1; ++c) {
+                const int n = cst[c];
+                cst[c] = before;
+                before += n;
+            }
+            if (tid == 0) cst[ncell] = rn;
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < kPer; ++u) {
+                const int k = tid + u * bs;
+                if (k < rn) tmp[cst[cs[u] & 4095u] + (int)(cs[u] >> 12)] = (uint16_t)k;
+            }
+            __syncthreads();
+            // an atom's place in its cell: the members with lower ids.  The
+            // record goes there with its id, and every share-th member in
+            // [a0, a1) opens a work entry
+#pragma unroll
+            for (int u = 0; u < kPer; ++u) {
+                const int k = tid + u * bs;
+                if (k >= rn) continue;
+                const int c = (int)(cs[u] & 4095u);
+                const int b = cst[c], m = cst[c + 1] - b;
+                int rank = 0, lo = 0;   // members below k, below a0
+                for (int t0 = 0; t0 < m; t0 += 8) {
+#pragma unroll
+                    for (int t = 0; t < 8; ++t) {   // reads past the cell repeat its last member
+                        const int x = (int)tmp[b + min(t0 + t, m - 1)];
+                        rank += t0 + t < m && x < k;
+                        lo += t0 + t < m && x < a0;
+                    }
+                }
+                st[b + rank] = make_uint4(qx[u], qy[u], qz[u], (uint32_t)k);
+                if (k >= a0 && k < a1 && (rank - lo) % share == 0)
+                    work[atomicAdd(&sh_n, 1)] = (uint32_t)(b + rank) << 12 | (uint32_t)c;
+                if (m > 64) atomicOr(a.status, ST_CELL_OVERFLOW);   // only overlapping atoms crowd a cell so
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < kPer; ++u) {
+                const int k = tid + u * bs;
+                if (k < rn) st[k] = make_uint4(qx[u], qy[u], qz[u], (uint32_t)k);
+            }
+        }
+    }
+    // the lists' reference positions (a load per atom in the loop below would
+    // make its wavefront wait for the row stores before it)
+    for (int k = a0 + tid; k < a1; k += bs) {
+        const double4 p = a.P[roff + k];
+        a.xref[roff + k] = p.x;
+        a.xref[a.N + roff + k] = p.y;
+        a.xref[2 * a.N + roff + k] = p.z;
+    }
+    __syncthreads();
+    // entries: (first member's place, cell), or for all-pairs rows shares of
+    // [a0, a1) in id order
+    const int ap_share = nc0 > 0 ? share : (a1 - a0 + nw - 1) / nw;
+    const int n_work = nc0 > 0 ? sh_n : (a1 - a0 + ap_share - 1) / max(1, ap_share);
+    for (;;) {
+        int f = 0;
+        if (lw == 0) f = atomicAdd(&sh_next, 1);
+        f = __builtin_amdgcn_readfirstlane(f);
+        if (f >= n_work) break;
+        // the entry's members, and its candidate stream's length and runs
+        int m0, m1, total, start = 0, nA = 0, nB = 0, sA = 0, sB = 0;
+        if (nc0 > 0) {
+            const uint32_t e = (uint32_t)__builtin_amdgcn_readfirstlane((int)work[f]);
+            const int c = (int)(e & 4095u);
+            m0 = (int)(e >> 12);
+            m1 = min(m0 + share, __builtin_amdgcn_readfirstlane(cst[c + 1]));
+            const int cz = c % nc2, cy = (c / nc2) % nc1, cx = c / (nc1 * nc2);
+            // lanes l and 32 + l hold line l of the stencil (25 lines along z)
+            const int l = lw & 31;
+            if (l < 25) {
+                const int base = (wrap_cell(cx + l / 5 - 2, nc0) * nc1 + wrap_cell(cy + l % 5 - 2, nc1)) * nc2;
+                const int z0 = cz - 2, z1 = cz + 2;
+                const bool wraps = z0 < 0 || z1 >= nc2;
+                const int za = z0 < 0 ? z0 + nc2 : z0, zb = wraps ? nc2 - 1 : z1;   // first run
+                const int zc = wraps ? (z0 < 0 ? z1 : z1 - nc2) : -1;               // and 0..zc, if it wraps
+                sA = cst[base + za];
+                nA = cst[base + zb + 1] - sA;
+                sB = cst[base];
+                nB = cst[base + zc + 1] - sB;
+            }
+            const int len = lw < 32 ? nA + nB : 0;
+            const int incl = wave_scan(len);
+            total = __builtin_amdgcn_readlane(incl, 63);
+            start = __shfl(incl - len, l, 64);   // both lanes of a line
+        } else {
+            m0 = a0 + f * ap_share;
+            m1 = min(m0 + ap_share, a1);
+            total = rn;
+        }
+        auto load = [&](auto& ch, int base) {
+            constexpr int K = std::decay_t<decltype(ch)>::n;
+            if (nc0 > 0) {
+                __builtin_amdgcn_wave_barrier();
+                const int odd = lw >> 5;
+                for (int t = odd; t < nA; t += 2) {
+                    const int pos = start + t - base;
+                    if ((unsigned)pos < 64u * K) stream[pos] = (uint16_t)(sA + t);
+                }
+                for (int t = odd; t < nB; t += 2) {
+                    const int pos = start + nA + t - base;
+                    if ((unsigned)pos < 64u * K) stream[pos] = (uint16_t)(sB + t);
+                }
+                __builtin_amdgcn_wave_barrier();
+            }
+            const int left = total - base;
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                uint4 q = make_uint4(0u, 0u, 0u, 0xffffu);
+                if (64 * k < left) {   // uniform
+                    const bool in = lw < left - 64 * k;
+                    q = st[!in ? 0 : nc0 > 0 ? (int)stream_l[64 * k] : base + 64 * k + lw];
+                    q.w = in ? q.w : 0xffffu;
+                }
+                ch.x[k] = q.x;
+                ch.y[k] = q.y;
+                ch.z[k] = q.z;
+                ch.id[k >> 1] = k & 1 ? ch.id[k >> 1] | q.w << 16 : q.w;
+            }
+        };
+        // the chunk's members in range of atom il, appended to the row
+        int cnt = 0;
+        auto test = [&](const auto& ch, const uint4& qi, int base) {
+            constexpr int K = std::decay_t<decltype(ch)>::n;
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                if (64 * k < total - base) {   // uniform
+                    const float dx = (float)(int)(qi.x - ch.x[k]) * g.sx, dy = (float)(int)(qi.y - ch.y[k]) * g.sy,
+                                dz = (float)(int)(qi.z - ch.z[k]) * g.sz;
+                    // (the empty asm keeps the unpacked ids of all k out of the atoms'
+                    // loop's registers)
+                    uint32_t pk = ch.id[k >> 1];
+                    __asm__ volatile("" : "+v"(pk));
+                    const uint32_t id = k & 1 ? pk >> 16 : pk & 0xffffu;
+                    const bool acc = id != qi.w && id != 0xffffu && dx * dx + dy * dy + dz * dz < a.rl2_f;
+                    const uint64_t m = __ballot(acc);
+                    const int slot = cnt + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                                     __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+                    if (acc && slot < a.cap) row[slot] = roff + (int)id;
+                    cnt += __popcll(m);
+                }
+            }
+        };
+        auto write = [&](int i) {
+            __builtin_amdgcn_wave_barrier();
+            // pad the last slab with the atom itself (cap is a multiple of 32), then
+            // write the row as whole slabs
+            const int used = cnt < a.cap ? cnt : a.cap;
+            const int pad_end = min((used + 3) & ~3, a.cap);
+            if (used + lw < pad_end) row[used + lw] = i;
+            __builtin_amdgcn_wave_barrier();
+            for (int b = lw; 4 * b < pad_end; b += 64)
+                *(int4*)(a.nbr + ((size_t)b * (size_t)a.N + (size_t)i) * 4) =
+                    make_int4(row[4 * b], row[4 * b + 1], row[4 * b + 2], row[4 * b + 3]);
+            if (lw == 0) {
+                if (cnt > a.cap) {
+                    atomicOr(a.status, ST_NEIGH_OVERFLOW);
+                    cnt = a.cap;
+                }
+                a.nnb[i] = cnt;
+            }
+            __builtin_amdgcn_wave_barrier();   // the row buffer is reused by the next atom
+        };
+        // members past a1 are past the share's last one (ids ascend in a cell)
+        if (total <= kRowsStream) {   // the whole stream stays in registers
+            RowsChunk<kCand> ch;
+            load(ch, 0);
+            for (int mb = m0; mb < m1; ++mb) {
+                const uint4 qi = st[mb];
+                if ((int)qi.w >= a1) break;
+                cnt = 0;
+                test(ch, qi, 0);
+                write(roff + (int)qi.w);
+            }
+        } else {
+            for (int mb = m0; mb < m1; ++mb) {
+                const uint4 qi = st[mb];
+                if ((int)qi.w >= a1) break;
+                cnt = 0;
+                for (int base = 0; base < total; base += 64 * 4) {   // small chunks: few registers
+                    RowsChunk<4> ch;
+                    load(ch, base);
+                    test(ch, qi, base);
+                }
+                write(roff + (int)qi.w);
+            }
+        }
+    }
+}
+
+// The LDS builder as a pass of its own.  The grid is one block per CU; every
+// block reads the rebuild flags of these replicas, splits the flagged ones
+// into `parts` slices of atoms so that the items fill the grid, and takes
+// items in a fixed stride.
+template <int kPer>
+__global__ __launch_bounds__(kRowsAtomsMax / kPer) void k_rows_lds(NeighArgs a, StepArgs s)
 {
     extern __shared__ uint4 lds_rows[];
-    const int lw = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    uint4* st = lds_rows;
-    uint16_t* ids = (uint16_t*)(st + a.lds_atoms);
-    int* cst = (int*)((char*)ids + (((size_t)a.lds_atoms * 2 + 15) & ~(size_t)15));
-    int* row = (int*)((char*)cst + (((size_t)(a.lds_cells + 1) * 4 + 15) & ~(size_t)15) +
-                      (size_t)w * rows_lds_wave_bytes(a.cap));
+    const int lw = threadIdx.x & 63, w = threadIdx.x >> 6;
     __shared__ int sh_nf, sh_atoms, sh_items, sh_rep, sh_part, sh_parts, sh_roff, sh_rn;
-    __shared__ int wsum[16];
     // the builder's k-th replica: the list holds them in replica order, so
     // when it holds every replica it is the identity, and the flag and size
     // reads need not wait for it
@@ -1082,212 +1362,233 @@ __global__ __launch_bounds__(1024) void k_rows_lds(NeighArgs a, StepArgs s)
         s.row_acc[a.n_rep + 1] += (double)nf;
         s.row_acc[a.n_rep + 2] += (double)atoms_f;
     }
-    const uint64_t below = (1ull << lw) - 1ull;
-    const float rl2 = a.rl2_f;
     for (int it = blockIdx.x; it < items; it += G) {
         if (it != (int)blockIdx.x) {   // a later item of this block (the first one is selected above)
             if (w == 0) select(it, atoms_f);
             __syncthreads();
         }
         const int rr = sh_rep, part = sh_part, parts = sh_parts, roff = sh_roff, rn = sh_rn;
-        const RepDesc& R = a.reps[rr];
-        // the cell counts and box go out with the record copy's loads
-        const int nc0 = R.nc[0], nc1 = R.nc[1], nc2 = R.nc[2];
-        const float sx = (float)(R.L[0] * 2.3283064365386963e-10), sy = (float)(R.L[1] * 2.3283064365386963e-10),
-                    sz = (float)(R.L[2] * 2.3283064365386963e-10);
-        copy_rounds<4, uint4>(rn, [&](int k) { return a.Q[roff + k]; }, [&](int k, const uint4& q) { st[k] = q; });
-        const int ncell = nc0 * nc1 * nc2;
-        if (nc0 > 0)
-            for (int c = threadIdx.x; c <= ncell; c += blockDim.x) cst[c] = 0;
-        __syncthreads();
-        auto cell_of = [&](const uint4& q) {
-            return (box_cell(q.x, nc0) * nc1 + box_cell(q.y, nc1)) * nc2 + box_cell(q.z, nc2);
-        };
-        if (nc0 > 0) {
-            for (int k = threadIdx.x; k < rn; k += blockDim.x) atomicAdd(&cst[cell_of(st[k])], 1);
-            __syncthreads();
-            // inclusive scan of the counts over the cells: contiguous segments
-            // per thread, then the segment totals across the block
-            {
-                const int per = (ncell + (int)blockDim.x - 1) / (int)blockDim.x;
-                const int c0 = threadIdx.x * per, c1 = min(ncell, c0 + per);
-                int tot = 0;
-                for (int c = c0; c < c1; ++c) tot += cst[c];
-                int incl = wave_scan(tot);
-                if (lw == 63) wsum[w] = incl;
-                __syncthreads();
-                int before = incl - tot;
-                for (int q = 0; q < w; ++q) before += wsum[q];
-                for (int c = c0; c < c1; ++c) {
-                    before += cst[c];
-                    cst[c] = before;
-                }
-                __syncthreads();
-            }
-            if (threadIdx.x == 0) cst[ncell] = rn;
-            // scatter: each cell's end pointer walks down to its start
-            for (int k = threadIdx.x; k < rn; k += blockDim.x) {
-                const int pos = atomicSub(&cst[cell_of(st[k])], 1) - 1;
-                ids[pos] = (uint16_t)k;
-            }
-            __syncthreads();
-            // each cell's members in id order: up to eight in registers through
-            // a sorting network (Batcher's odd-even merge; their reads in flight
-            // together), an insertion sort in LDS beyond
-            for (int c = threadIdx.x; c < ncell; c += blockDim.x) {
-                const int b = cst[c], e = cst[c + 1], m = e - b;
-                if (m <= 1) continue;
-                if (m <= 8) {
-                    int v[8];
+        build_rows<kPer>(a, rows_geom(a.reps[rr]), [&](int k) { return a.Q[roff + k]; }, lds_rows,
+                         (char*)(lds_rows + a.lds_atoms), (int)((long long)rn * part / parts),
+                         (int)((long long)rn * (part + 1) / parts));
+        if (it + G < items) __syncthreads();   // the sorted replica is replaced by the next item's
+    }
+}
+
+// --------------------------------------------------------------------------
+// The pair sums of one lane's share of an atom's row, for the density and
+// force passes and the persistent step kernel alike: records from P or Q
+// (record j - qoff), table intervals from tab4 / tab8.
+// --------------------------------------------------------------------------
+struct Scale3 {   // box coordinate -> Angstrom, per axis
+    float x, y, z;
+};
+
+__device__ __forceinline__ Scale3 box_scale(const RepDesc& R)
+{
+    return Scale3{(float)(R.L[0] * 2.3283064365386963e-10), (float)(R.L[1] * 2.3283064365386963e-10),
+                  (float)(R.L[2] * 2.3283064365386963e-10)};
+}
+
+// sum_j rho(r_ij) (in the accumulator's form); tab4(m): rho's coefficients
+template <typename real, int T, bool kFix, typename Tab4>
+__device__ __forceinline__ double density_walk(const StepArgs& a, const RepDesc& R, const double4& pi, const uint4& qi,
+                                               const Scale3& q, const double4* P, const uint4* Q, int qoff, int i,
+                                               int lane, int n, Tab4&& tab4)
+{
+    constexpr bool kQ = sizeof(real) == 4;
+    const int nr = a.tab.n_r;
+    double acc = 0.0;
+    const real rc2 = (real)a.tab.rc2, inv_h = (real)a.tab.inv_h_r;
+    const uint32_t rc2m1 = __float_as_uint((float)a.tab.rc2) - 1u;   // FP32 form's cutoff test
+    walk_row<kQ, T>(a.nbr, P, Q, qoff, a.N, i, lane, n, [&](const Nb<kQ>& g, int b0) {
+        real r[SB], t[SB];
+        int m[SB];
+        bool in[SB];
 #pragma unroll
-                    for (int t = 0; t < 8; ++t) v[t] = t < m ? (int)ids[b + t] : 0xffff;
-                    auto cmpx = [&](int p, int q) {
-                        const int lo = min(v[p], v[q]), hi = max(v[p], v[q]);
-                        v[p] = lo;
-                        v[q] = hi;
-                    };
-                    cmpx(0, 1); cmpx(2, 3); cmpx(4, 5); cmpx(6, 7);
-                    cmpx(0, 2); cmpx(1, 3); cmpx(4, 6); cmpx(5, 7);
-                    cmpx(1, 2); cmpx(5, 6);
-                    cmpx(0, 4); cmpx(1, 5); cmpx(2, 6); cmpx(3, 7);
-                    cmpx(2, 4); cmpx(3, 5);
-                    cmpx(1, 2); cmpx(3, 4); cmpx(5, 6);
-#pragma unroll
-                    for (int t = 0; t < 8; ++t)
-                        if (t < m) ids[b + t] = (uint16_t)v[t];
-                } else {
-                    for (int t = b + 1; t < e; ++t) {
-                        const uint16_t x = ids[t];
-                        int u = t;
-                        while (u > b && ids[u - 1] > x) {
-                            ids[u] = ids[u - 1];
-                            --u;
-                        }
-                        ids[u] = x;
-                    }
-                }
+        for (int s = 0; s < SB; ++s) {
+            real rx, ry, rz;
+            if constexpr (kQ) {
+                rx = (real)(int)(qi.x - g.v[s].x) * q.x;
+                ry = (real)(int)(qi.y - g.v[s].y) * q.y;
+                rz = (real)(int)(qi.z - g.v[s].z) * q.z;
+            } else {
+                const double3 d = sep(R, pi, g.v[s]);
+                rx = (real)d.x;
+                ry = (real)d.y;
+                rz = (real)d.z;
+            }
+            const real r2 = rx * rx + ry * ry + rz * rz;
+            real ir;
+            if constexpr (kQ) {
+                // 0 < r^2 < rc^2 in one unsigned compare of the bits; the
+                // self-padded slots of a row's last slab give r^2 = 0
+                in[s] = __float_as_uint(r2) - 1u < rc2m1;
+                Root<real>::of(in[s] ? r2 : (real)1, r[s], ir);
+                m[s] = interval_pad(r[s], inv_h, t[s]);
+            } else {
+                in[s] = (b0 + s < n) && r2 < rc2;
+                Root<real>::of(r2, r[s], ir);
+                m[s] = interval<real>(in[s] ? r[s] : (real)0, inv_h, nr, t[s]);
             }
         }
-        __syncthreads();
-        // rows of this item's atoms, one wavefront per atom
-        const int a0 = (int)((long long)rn * part / parts), a1 = (int)((long long)rn * (part + 1) / parts);
-        for (int il = a0 + w; il < a1; il += nw) {
-            const int i = roff + il;
-            const uint4 qi = st[il];
-            const double4 pi = a.P[i];   // the list's reference position, read ahead of the row work
-            auto close_to = [&](const uint4& qj) {
-                const float dx = (float)(int)(qi.x - qj.x) * sx, dy = (float)(int)(qi.y - qj.y) * sy,
-                            dz = (float)(int)(qi.z - qj.z) * sz;
-                return dx * dx + dy * dy + dz * dz < rl2;
-            };
-            int cnt = 0;
-            if (nc0 == 0) {   // all-pairs rows: every other atom in id order
-                for (int s0 = 0; s0 < rn; s0 += 64) {
-                    const int jl = s0 + lw;
-                    const bool acc = jl < rn && jl != il && close_to(st[jl < rn ? jl : il]);
-                    const uint64_t m = __ballot(acc);
-                    const int rank = __popcll(m & below);
-                    if (acc && cnt + rank < a.cap) row[cnt + rank] = roff + jl;
-                    cnt += __popcll(m);
+        real part = (real)0;
+#pragma unroll
+        for (int s = 0; s < SB; ++s) {
+            const auto c = tab4(m[s]);
+            const real v = c.x + t[s] * (c.y + t[s] * (c.z + t[s] * c.w));
+            if constexpr (kQ) part += v * (in[s] ? 1.f : 0.f);   // a product: the table read stays unconditional
+            else part += in[s] ? v : (real)0;
+        }
+        acc += Acc<real, kFix>::q(part);
+    });
+    return acc;
+}
+
+// One interval of the pair table: phi's coefficients and those of rho'.
+template <typename real>
+struct PairCoef {
+    real ua, ub, uc, ud, wb, wc, wd;
+};
+
+// Sums over the row of the pair + embedding force, of phi and (kVir) of the
+// virial's diagonal, added to f[0..2], f[3] and w; tab8(m): a PairCoef
+template <typename real, int T, bool kVir, bool kFix, typename Tab8>
+__device__ __forceinline__ void force_walk(const StepArgs& a, const RepDesc& R, const double4& pi, const uint4& qi,
+                                           const Scale3& q, const double4* P, const uint4* Q, int qoff, int i,
+                                           int lane, int n, Tab8&& tab8, double (&f)[4], double (&w)[3])
+{
+    constexpr bool kQ = sizeof(real) == 4;
+    const int nr = a.tab.n_r;
+    const real Fpi = kQ ? (real)__uint_as_float(qi.w) : (real)pi.w;
+    const real rc2 = (real)a.tab.rc2, inv_h = (real)a.tab.inv_h_r;
+    const uint32_t rc2m1 = __float_as_uint((float)a.tab.rc2) - 1u;   // FP32 form's cutoff test
+    walk_row<kQ, T>(a.nbr, P, Q, qoff, a.N, i, lane, n, [&](const Nb<kQ>& g, int b0) {
+        real rx[SB], ry[SB], rz[SB], ir[SB], t[SB], fpj[SB];
+        int m[SB];
+        bool in[SB];
+#pragma unroll
+        for (int s = 0; s < SB; ++s) {
+            if constexpr (kQ) {
+                rx[s] = (real)(int)(qi.x - g.v[s].x) * q.x;
+                ry[s] = (real)(int)(qi.y - g.v[s].y) * q.y;
+                rz[s] = (real)(int)(qi.z - g.v[s].z) * q.z;
+                fpj[s] = (real)__uint_as_float(g.v[s].w);
+            } else {
+                const double3 d = sep(R, pi, g.v[s]);
+                rx[s] = (real)d.x;
+                ry[s] = (real)d.y;
+                rz[s] = (real)d.z;
+                fpj[s] = (real)g.v[s].w;
+            }
+            const real r2 = rx[s] * rx[s] + ry[s] * ry[s] + rz[s] * rz[s];
+            real r;
+            if constexpr (kQ) {
+                in[s] = __float_as_uint(r2) - 1u < rc2m1;   // 0 < r^2 < rc^2, as in the density pass
+                Root<real>::of(in[s] ? r2 : (real)1, r, ir[s]);
+                m[s] = interval_pad(r, inv_h, t[s]);
+            } else {
+                in[s] = (b0 + s < n) && r2 < rc2;
+                Root<real>::of(in[s] ? r2 : (real)1, r, ir[s]);
+                m[s] = interval<real>(in[s] ? r : (real)0, inv_h, nr, t[s]);
+            }
+        }
+        real p0 = (real)0, p1 = (real)0, p2 = (real)0, pe = (real)0;
+        real q0 = (real)0, q1 = (real)0, q2 = (real)0;
+#pragma unroll
+        for (int s = 0; s < SB; ++s) {
+            const auto c = tab8(m[s]);
+            const real ua = c.ua, ub = c.ub, uc = c.uc, ud = c.ud, wb = c.wb, wc = c.wc, wd = c.wd;
+            const real ts = t[s];
+            if constexpr (kQ) {
+                // phi and h dphi/dr = b + 2 c t + 3 d t^2 share their Horner
+                // terms; pairs outside the cutoff are weighted by zero (a
+                // product, not a select, so every table read stays one 16-byte load)
+                const float cu = uc + ts * ud, cv = ub + ts * cu;
+                const float phi = ua + ts * cv;
+                const float dphi_h = cv + ts * (cu + ts * ud);
+                const float drho = wb + ts * (wc + ts * wd);
+                const float fm = in[s] ? 1.f : 0.f;
+                const float gr = dphi_h * inv_h + (Fpi + fpj[s]) * drho;   // dU/dr_ij
+                const float sc = -gr * (ir[s] * fm);
+                p0 += sc * rx[s];
+                p1 += sc * ry[s];
+                p2 += sc * rz[s];
+                pe += phi * fm;
+                if constexpr (kVir) {
+                    q0 += sc * rx[s] * rx[s];
+                    q1 += sc * ry[s] * ry[s];
+                    q2 += sc * rz[s] * rz[s];
                 }
             } else {
-                // lane l tests stencil cells l and 64 + l (cells by offset, the
-                // 125 of a 5 x 5 x 5 block), keeping a mask of its members in
-                // range; a prefix sum of the accepted counts over the cells then
-                // gives every accepted member its slot, so the row is the stream
-                // of cells in offset order, members in id order.  Five or more
-                // cells per edge: an offset of -2..2 wraps at most once.
-                const int cx = box_cell(qi.x, nc0), cy = box_cell(qi.y, nc1), cz = box_cell(qi.z, nc2);
-                int cb[2], cn[2];
-                uint64_t mask[2];
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const int q = 64 * h + lw;
-                    cb[h] = 0;
-                    cn[h] = 0;
-                    mask[h] = 0ull;
-                    if (q < kStencil) {
-                        const int ux = wrap_cell(cx + q / 25 - 2, nc0);
-                        const int uy = wrap_cell(cy + (q / 5) % 5 - 2, nc1);
-                        const int uz = wrap_cell(cz + q % 5 - 2, nc2);
-                        const int c = (ux * nc1 + uy) * nc2 + uz;
-                        cb[h] = cst[c];
-                        cn[h] = cst[c + 1] - cb[h];
-                        if (cn[h] > 64) {   // a mask holds 64 members (only overlapping atoms crowd a cell so)
-                            atomicOr(a.status, ST_CELL_OVERFLOW);
-                            cn[h] = 64;
-                        }
-                    }
+                const real phi = ua + ts * (ub + ts * (uc + ts * ud));
+                const real dphi = (ub + ts * ((real)2 * uc + (real)3 * ts * ud)) * inv_h;
+                const real drho = wb + ts * (wc + ts * wd);
+                const real gr = dphi + (Fpi + fpj[s]) * drho;   // dU/dr_ij
+                const real sc = in[s] ? -gr * ir[s] : (real)0;
+                p0 += sc * rx[s];
+                p1 += sc * ry[s];
+                p2 += sc * rz[s];
+                pe += in[s] ? phi : (real)0;
+                if constexpr (kVir) {
+                    q0 += sc * rx[s] * rx[s];
+                    q1 += sc * ry[s] * ry[s];
+                    q2 += sc * rz[s] * rz[s];
                 }
-                // both cells' members four at a time: their id and record reads
-                // in flight together
-                for (int t0 = 0; t0 < max(cn[0], cn[1]); t0 += 4) {
-                    int jl[2][4];
-                    uint4 qj[2][4];
-#pragma unroll
-                    for (int h = 0; h < 2; ++h)
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) jl[h][u] = t0 + u < cn[h] ? (int)ids[cb[h] + t0 + u] : il;
-#pragma unroll
-                    for (int h = 0; h < 2; ++h)
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) qj[h][u] = st[jl[h][u]];
-#pragma unroll
-                    for (int h = 0; h < 2; ++h)
-#pragma unroll
-                        for (int u = 0; u < 4; ++u)
-                            if (jl[h][u] != il && close_to(qj[h][u])) mask[h] |= 1ull << (t0 + u);
-                }
-                int base = 0;
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const int n_acc = __popcll(mask[h]);
-                    int incl = wave_scan(n_acc);
-                    int slot = base + incl - n_acc;
-                    if (cn[h] <= 8) {   // the first eight members: reads in flight together
-                        int id8[8];
-#pragma unroll
-                        for (int t = 0; t < 8; ++t) id8[t] = (int)ids[cb[h] + min(t, max(cn[h] - 1, 0))];
-#pragma unroll
-                        for (int t = 0; t < 8; ++t)
-                            if ((mask[h] >> t) & 1ull) {
-                                if (slot < a.cap) row[slot] = roff + id8[t];
-                                ++slot;
-                            }
-                    } else {
-                        for (uint64_t m = mask[h]; m; m &= m - 1ull) {
-                            const int t = (int)__ffsll((long long)m) - 1;
-                            if (slot < a.cap) row[slot] = roff + (int)ids[cb[h] + t];
-                            ++slot;
-                        }
-                    }
-                    base += __builtin_amdgcn_readlane(incl, 63);
-                }
-                cnt = base;
             }
-            __builtin_amdgcn_wave_barrier();
-            // pad the last slab with the atom itself (cap is a multiple of 32), then
-            // write the row as whole slabs
-            const int used = cnt < a.cap ? cnt : a.cap;
-            const int pad_end = min((used + 3) & ~3, a.cap);
-            if (used + lw < pad_end) row[used + lw] = i;
-            __builtin_amdgcn_wave_barrier();
-            for (int b = lw; 4 * b < pad_end; b += 64)
-                *(int4*)(a.nbr + ((size_t)b * (size_t)a.N + (size_t)i) * 4) =
-                    make_int4(row[4 * b], row[4 * b + 1], row[4 * b + 2], row[4 * b + 3]);
-            if (lw == 0) {
-                if (cnt > a.cap) {
-                    atomicOr(a.status, ST_NEIGH_OVERFLOW);
-                    cnt = a.cap;
-                }
-                a.nnb[i] = cnt;
-                a.xref[i] = pi.x;
-                a.xref[a.N + i] = pi.y;
-                a.xref[2 * a.N + i] = pi.z;
-            }
-            __builtin_amdgcn_wave_barrier();   // the row buffer is reused by the next atom
         }
-        if (it + G < items) __syncthreads();   // the staged replica is replaced by the next item's
+        f[0] += Acc<real, kFix>::q(p0);
+        f[1] += Acc<real, kFix>::q(p1);
+        f[2] += Acc<real, kFix>::q(p2);
+        f[3] += Acc<real, kFix>::q(pe);
+        if constexpr (kVir) {
+            w[0] += Acc<real, kFix>::q(q0);
+            w[1] += Acc<real, kFix>::q(q1);
+            w[2] += Acc<real, kFix>::q(q2);
+        }
+    });
+}
+
+// F(rho) and F'(rho) from the embedding table's interval c at local coordinate t.
+template <typename real, typename C>
+__device__ __forceinline__ void embed(const C& c, real t, double inv_h_rho, real& F, real& Fp)
+{
+    F = c.x + t * (c.y + t * (c.z + t * c.w));
+    Fp = (c.y + t * ((real)2 * c.z + (real)3 * t * c.w)) * (real)inv_h_rho;
+}
+
+// The thermostat deviates of step `it` for the lanes of an atom: lane 0 returns
+// the x and y components, lane 1 z (one lane per atom: lane 0 all three), on
+// the 2^-36 grid where `grid`; the values go to xi.
+template <int T>
+__device__ __forceinline__ void draw_noise(uint64_t seed, uint32_t atom, int64_t it, int lane, bool valid, bool grid,
+                                           double* xi, int N, int i, double (&z)[3])
+{
+    z[0] = z[1] = z[2] = 0.0;
+    if constexpr (T == 1) {
+        if (valid) {
+            gauss3(seed, atom, it, 0u, z[0], z[1], z[2]);
+            if (grid) on_grid<3>(z, kGridZ, kGridZInv);
+            xi[i] = z[0];
+            xi[N + i] = z[1];
+            xi[2 * N + i] = z[2];
+        }
+    } else if (valid && lane < 2) {   // lane 0: x and y components, lane 1: z
+        double za, zb;
+        gauss3_half(seed, atom, it, 0u, lane, za, zb);
+        if (grid) {
+            za = rint(za * kGridZ) * kGridZInv;
+            zb = rint(zb * kGridZ) * kGridZInv;
+        }
+        if (lane == 0) {
+            z[0] = za;
+            z[1] = zb;
+            xi[i] = za;
+            xi[N + i] = zb;
+        } else {
+            z[2] = za;
+            xi[2 * N + i] = za;
+        }
     }
 }
 
@@ -1333,61 +1634,13 @@ __global__ __launch_bounds__(kMaxBlock) void k_density(StepArgs a)
     double acc = 0.0;
     const double4 pi = a.P[i];
     const uint4 qi = kQ ? a.Q[i] : make_uint4(0u, 0u, 0u, 0u);
-    const float qsx = (float)(R.L[0] * 2.3283064365386963e-10), qsy = (float)(R.L[1] * 2.3283064365386963e-10),
-                qsz = (float)(R.L[2] * 2.3283064365386963e-10);
-    if (valid && a.has_eam) {
-        const int n = a.nnb[i];
-        const real rc2 = (real)a.tab.rc2, inv_h = (real)a.tab.inv_h_r;
-        const uint32_t rc2m1 = __float_as_uint((float)a.tab.rc2) - 1u;   // FP32 form's cutoff test
-        walk_row<kQ, T>(a.nbr, a.P, kStage ? st : a.Q, kStage ? R.off : 0, N, i, lane, n,
-                        [&](const Nb<kQ>& g, int b0) {
-            real r[SB], t[SB];
-            int m[SB];
-            bool in[SB];
-#pragma unroll
-            for (int s = 0; s < SB; ++s) {
-                real rx, ry, rz;
-                if constexpr (kQ) {
-                    rx = (real)(int)(qi.x - g.v[s].x) * qsx;
-                    ry = (real)(int)(qi.y - g.v[s].y) * qsy;
-                    rz = (real)(int)(qi.z - g.v[s].z) * qsz;
-                } else {
-                    const double3 d = sep(R, pi, g.v[s]);
-                    rx = (real)d.x;
-                    ry = (real)d.y;
-                    rz = (real)d.z;
-                }
-                const real r2 = rx * rx + ry * ry + rz * rz;
-                real ir;
-                if constexpr (kQ) {
-                    // 0 < r^2 < rc^2 in one unsigned compare of the bits; the
-                    // self-padded slots of a row's last slab give r^2 = 0
-                    in[s] = __float_as_uint(r2) - 1u < rc2m1;
-                    Root<real>::of(in[s] ? r2 : (real)1, r[s], ir);
-                    m[s] = interval_pad(r[s], inv_h, t[s]);
-                } else {
-                    in[s] = (b0 + s < n) && r2 < rc2;
-                    Root<real>::of(r2, r[s], ir);
-                    m[s] = interval<real>(in[s] ? r[s] : (real)0, inv_h, nr, t[s]);
-                }
-            }
-            real part = (real)0;
-#pragma unroll
-            for (int s = 0; s < SB; ++s) {
-                real v;
-                if constexpr (kLds && kQ) {
-                    const float4 c = lds_tab[m[s]];
-                    v = c.x + t[s] * (c.y + t[s] * (c.z + t[s] * c.w));
-                } else {
-                    const auto c = Tab<real>::ld4(kLds ? (const void*)lds_tab : a.tab.rho, m[s]);
-                    v = c.x + t[s] * (c.y + t[s] * (c.z + t[s] * c.w));
-                }
-                if constexpr (kQ) part += v * (in[s] ? 1.f : 0.f);   // a product: the table read stays unconditional
-                else part += in[s] ? v : (real)0;
-            }
-            acc += Acc<real, kFix>::q(part);
-        });
-    }
+    const Scale3 q = box_scale(R);
+    if (valid && a.has_eam)
+        acc = density_walk<real, T, kFix>(a, R, pi, qi, q, a.P, kStage ? st : a.Q, kStage ? R.off : 0, i, lane,
+                                          a.nnb[i], [&](int m) {
+                                              if constexpr (kLds && kQ) return lds_tab[m];
+                                              else return Tab<real>::ld4(kLds ? (const void*)lds_tab : a.tab.rho, m);
+                                          });
 #pragma unroll
     for (int o = T / 2; o > 0; o >>= 1) acc += xor_lanes(acc, o);   // (o < T: the partner is in the atom's lanes)
     // one memory round trip for the epilogue: the embedding table's interval
@@ -1424,40 +1677,14 @@ __global__ __launch_bounds__(kMaxBlock) void k_density(StepArgs a)
     // the mean the step removes is the exact mean of the values it applies
     // (a lone atom stays put bit for bit)
     if (a.step_kernel && it < a.it_last) {
-        constexpr bool kGrid = sizeof(real) == 4 && kFix;
-        double z[3] = {0.0, 0.0, 0.0};
-        if constexpr (T == 1) {
-            if (valid) {
-                gauss3(seed, (uint32_t)(i - roff), it, 0u, z[0], z[1], z[2]);
-                if (kGrid && a.fix_com) on_grid<3>(z, kGridZ, kGridZInv);
-                a.xi[i] = z[0];
-                a.xi[N + i] = z[1];
-                a.xi[2 * N + i] = z[2];
-            }
-        } else if (valid && lane < 2) {   // lane 0: x and y components, lane 1: z
-            double za, zb;
-            gauss3_half(seed, (uint32_t)(i - roff), it, 0u, lane, za, zb);
-            if (kGrid && a.fix_com) {
-                za = rint(za * kGridZ) * kGridZInv;
-                zb = rint(zb * kGridZ) * kGridZInv;
-            }
-            if (lane == 0) {
-                z[0] = za;
-                z[1] = zb;
-                a.xi[i] = za;
-                a.xi[N + i] = zb;
-            } else {
-                z[2] = za;
-                a.xi[2 * N + i] = za;
-            }
-        }
+        double z[3];
+        draw_noise<T>(seed, (uint32_t)(i - roff), it, lane, valid, sizeof(real) == 4 && kFix && a.fix_com, a.xi, N, i,
+                      z);
         if (a.fix_com) unit_partial<3>(z, a.noise_part, tbase, tl.idx);
     }
     if (emb) {
-        const auto& c = cF;
-        const real t = tF;
-        const real F = c.x + t * (c.y + t * (c.z + t * c.w));
-        const real Fp = (c.y + t * ((real)2 * c.z + (real)3 * t * c.w)) * (real)a.tab.inv_h_rho;
+        real F, Fp;
+        embed<real>(cF, tF, a.tab.inv_h_rho, F, Fp);
         if constexpr (kQ) a.Q[i].w = __float_as_uint((float)Fp);
         else a.P[i].w = (double)Fp;
         a.e_emb[i] = (double)F;
@@ -1538,119 +1765,29 @@ __global__ __launch_bounds__(kMaxBlock) void k_force(StepArgs a)
     // that the noise partials' loads need no descriptor read after it
     const int tbase = __builtin_amdgcn_readfirstlane(R.tile_base);
     const int ntile = __builtin_amdgcn_readfirstlane(R.n_tiles);
-    const float qsx = (float)(R.L[0] * 2.3283064365386963e-10), qsy = (float)(R.L[1] * 2.3283064365386963e-10),
-                qsz = (float)(R.L[2] * 2.3283064365386963e-10);
-    double f0 = 0.0, f1 = 0.0, f2 = 0.0, ep = 0.0;
-    double w0 = 0.0, w1 = 0.0, w2 = 0.0;   // virial (kVir): sum_j (x_i - x_j)_a f_ij,a per axis
-    if (valid && a.has_eam) {
-        const int n = nrow;
-        const real Fpi = kQ ? (real)__uint_as_float(qi.w) : (real)pi.w;
-        const real rc2 = (real)a.tab.rc2, inv_h = (real)a.tab.inv_h_r;
-        const uint32_t rc2m1 = __float_as_uint((float)a.tab.rc2) - 1u;   // FP32 form's cutoff test
-        walk_row<kQ, T>(a.nbr, a.P, kStage ? st : a.Q, kStage ? R.off : 0, N, i, lane, n,
-                        [&](const Nb<kQ>& g, int b0) {
-            real rx[SB], ry[SB], rz[SB], ir[SB], t[SB], fpj[SB];
-            int m[SB];
-            bool in[SB];
+    const Scale3 q = box_scale(R);
+    double f[4] = {0.0, 0.0, 0.0, 0.0};   // force, pair energy
+    double w[3] = {0.0, 0.0, 0.0};        // virial (kVir): sum_j (x_i - x_j)_a f_ij,a per axis
+    if (valid && a.has_eam)
+        force_walk<real, T, kVir, kFix>(a, R, pi, qi, q, a.P, kStage ? st : a.Q, kStage ? R.off : 0, i, lane, nrow,
+                                        [&](int m) {
+                                            if constexpr (kLds && kQ) {
+                                                const float4 u = lds_tab[m], v = lds_tab[nr + m];
+                                                return PairCoef<real>{u.x, u.y, u.z, u.w, v.x, v.y, v.z};
+                                            } else {
+                                                decltype(Tab<real>::ld4(a.tab.rho, 0)) u, v;
+                                                Tab<real>::ld8(kLds ? (const void*)lds_tab : a.tab.pair, m, u, v);
+                                                return PairCoef<real>{u.x, u.y, u.z, u.w, v.x, v.y, v.z};
+                                            }
+                                        },
+                                        f, w);
 #pragma unroll
-            for (int s = 0; s < SB; ++s) {
-                if constexpr (kQ) {
-                    rx[s] = (real)(int)(qi.x - g.v[s].x) * qsx;
-                    ry[s] = (real)(int)(qi.y - g.v[s].y) * qsy;
-                    rz[s] = (real)(int)(qi.z - g.v[s].z) * qsz;
-                    fpj[s] = (real)__uint_as_float(g.v[s].w);
-                } else {
-                    const double3 d = sep(R, pi, g.v[s]);
-                    rx[s] = (real)d.x;
-                    ry[s] = (real)d.y;
-                    rz[s] = (real)d.z;
-                    fpj[s] = (real)g.v[s].w;
-                }
-                const real r2 = rx[s] * rx[s] + ry[s] * ry[s] + rz[s] * rz[s];
-                real r;
-                if constexpr (kQ) {
-                    in[s] = __float_as_uint(r2) - 1u < rc2m1;   // 0 < r^2 < rc^2, as in the density pass
-                    Root<real>::of(in[s] ? r2 : (real)1, r, ir[s]);
-                    m[s] = interval_pad(r, inv_h, t[s]);
-                } else {
-                    in[s] = (b0 + s < n) && r2 < rc2;
-                    Root<real>::of(in[s] ? r2 : (real)1, r, ir[s]);
-                    m[s] = interval<real>(in[s] ? r : (real)0, inv_h, nr, t[s]);
-                }
-            }
-            real p0 = (real)0, p1 = (real)0, p2 = (real)0, pe = (real)0;
-            real q0 = (real)0, q1 = (real)0, q2 = (real)0;
+    for (int o = T / 2; o > 0; o >>= 1) {   // (o < T: the partner is in the atom's lanes)
 #pragma unroll
-            for (int s = 0; s < SB; ++s) {
-                real ua, ub, uc, ud, wb, wc, wd;
-                if constexpr (kLds && kQ) {
-                    const float4 u = lds_tab[m[s]], w = lds_tab[nr + m[s]];
-                    ua = u.x; ub = u.y; uc = u.z; ud = u.w; wb = w.x; wc = w.y; wd = w.z;
-                } else {
-                    decltype(Tab<real>::ld4(a.tab.rho, 0)) u, w;
-                    Tab<real>::ld8(kLds ? (const void*)lds_tab : a.tab.pair, m[s], u, w);
-                    ua = u.x; ub = u.y; uc = u.z; ud = u.w; wb = w.x; wc = w.y; wd = w.z;
-                }
-                const real ts = t[s];
-                if constexpr (kQ) {
-                    // phi and h dphi/dr = b + 2 c t + 3 d t^2 share their Horner
-                    // terms; pairs outside the cutoff are weighted by zero (a
-                    // product, not a select, so every table read stays one 16-byte load)
-                    const float cu = uc + ts * ud, cv = ub + ts * cu;
-                    const float phi = ua + ts * cv;
-                    const float dphi_h = cv + ts * (cu + ts * ud);
-                    const float drho = wb + ts * (wc + ts * wd);
-                    const float fm = in[s] ? 1.f : 0.f;
-                    const float g = dphi_h * inv_h + (Fpi + fpj[s]) * drho;   // dU/dr_ij
-                    const float sc = -g * (ir[s] * fm);
-                    p0 += sc * rx[s];
-                    p1 += sc * ry[s];
-                    p2 += sc * rz[s];
-                    pe += phi * fm;
-                    if constexpr (kVir) {
-                        q0 += sc * rx[s] * rx[s];
-                        q1 += sc * ry[s] * ry[s];
-                        q2 += sc * rz[s] * rz[s];
-                    }
-                } else {
-                    const real phi = ua + ts * (ub + ts * (uc + ts * ud));
-                    const real dphi = (ub + ts * ((real)2 * uc + (real)3 * ts * ud)) * inv_h;
-                    const real drho = wb + ts * (wc + ts * wd);
-                    const real g = dphi + (Fpi + fpj[s]) * drho;   // dU/dr_ij
-                    const real sc = in[s] ? -g * ir[s] : (real)0;
-                    p0 += sc * rx[s];
-                    p1 += sc * ry[s];
-                    p2 += sc * rz[s];
-                    pe += in[s] ? phi : (real)0;
-                    if constexpr (kVir) {
-                        q0 += sc * rx[s] * rx[s];
-                        q1 += sc * ry[s] * ry[s];
-                        q2 += sc * rz[s] * rz[s];
-                    }
-                }
-            }
-            f0 += Acc<real, kFix>::q(p0);
-            f1 += Acc<real, kFix>::q(p1);
-            f2 += Acc<real, kFix>::q(p2);
-            ep += Acc<real, kFix>::q(pe);
-            if constexpr (kVir) {
-                w0 += Acc<real, kFix>::q(q0);
-                w1 += Acc<real, kFix>::q(q1);
-                w2 += Acc<real, kFix>::q(q2);
-            }
-        });
-    }
+        for (int k = 0; k < 4; ++k) f[k] += xor_lanes(f[k], o);
+        if constexpr (kVir)
 #pragma unroll
-    for (int o = T / 2; o > 0; o >>= 1) {
-        f0 += xor_lanes(f0, o);   // (o < T: the partner is in the atom's lanes)
-        f1 += xor_lanes(f1, o);
-        f2 += xor_lanes(f2, o);
-        ep += xor_lanes(ep, o);
-        if constexpr (kVir) {
-            w0 += xor_lanes(w0, o);
-            w1 += xor_lanes(w1, o);
-            w2 += xor_lanes(w2, o);
-        }
+            for (int k = 0; k < 3; ++k) w[k] += xor_lanes(w[k], o);
     }
 
     // the atom's operands of the integration and the replica's noise
@@ -1689,12 +1826,12 @@ __global__ __launch_bounds__(kMaxBlock) void k_force(StepArgs a)
 
     double e[3] = {0.0, 0.0, 0.0};   // U_EAM contribution, |x - x0|^2, row length (list work of the pass)
     if (valid && lane == 0) {
-        const double fe[3] = {Acc<real, kFix>::fin(f0), Acc<real, kFix>::fin(f1), Acc<real, kFix>::fin(f2)};
+        const double fe[3] = {Acc<real, kFix>::fin(f[0]), Acc<real, kFix>::fin(f[1]), Acc<real, kFix>::fin(f[2])};
         double x[3] = {pi.x, pi.y, pi.z};
         // the spring displacement weighted by the atom's spring scale: the
         // spring force is -k ks (x - x0) and its energy k ks |x - x0|^2 / 2
         const double d[3] = {ks * (x[0] - x0i[0]), ks * (x[1] - x0i[1]), ks * (x[2] - x0i[2])};
-        e[0] = a.has_eam ? eemb + 0.5 * Acc<real, kFix>::fin(ep) : 0.0;
+        e[0] = a.has_eam ? eemb + 0.5 * Acc<real, kFix>::fin(f[3]) : 0.0;
         e[1] = (d[0] * (x[0] - x0i[0]) + d[1] * (x[1] - x0i[1]) + d[2] * (x[2] - x0i[2]));
         e[2] = (double)nrow;
         if (!isfinite(fe[0] + fe[1] + fe[2] + e[0] + e[1])) atomicOr(a.status, ST_NONFINITE);
@@ -1741,7 +1878,7 @@ __global__ __launch_bounds__(kMaxBlock) void k_force(StepArgs a)
     if constexpr (kVir) {   // pressure evaluation: (1/2) pair virial plus m v_a^2 of the atom, per unit
         double pv[3] = {0.0, 0.0, 0.0};
         if (valid && lane == 0) {
-            const double wv[3] = {Acc<real, kFix>::fin(w0), Acc<real, kFix>::fin(w1), Acc<real, kFix>::fin(w2)};
+            const double wv[3] = {Acc<real, kFix>::fin(w[0]), Acc<real, kFix>::fin(w[1]), Acc<real, kFix>::fin(w[2])};
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
                 const double vc = a.v ? a.v[c * N + i] : 0.0;
@@ -1921,9 +2058,9 @@ int launch_neigh_rebuild(const NeighArgs& a, const StepArgs& st, int lanes, int 
     }
     if (a.n_lds > 0) {
         const size_t lds = rows_lds_bytes(a.lds_atoms, a.lds_cells, a.cap, a.lds_waves);
-        const void* f = reinterpret_cast<const void*>(&k_rows_lds);
-        allow_lds(f, lds);
-        hipLaunchKernelGGL(k_rows_lds, dim3(a.lds_grid), dim3(64 * a.lds_waves), lds, s, a, st);
+        const auto k = a.lds_waves >= 16 ? k_rows_lds<4> : a.lds_waves >= 8 ? k_rows_lds<8> : k_rows_lds<16>;
+        allow_lds(reinterpret_cast<const void*>(k), lds);
+        hipLaunchKernelGGL(k, dim3(a.lds_grid), dim3(64 * a.lds_waves), lds, s, a, st);
     }
     return (int)hipGetLastError();
 }
