@@ -77,6 +77,7 @@ struct eamfe_ctx {
     int deterministic = 1;   // FP32: 2^-32 fixed-point per-atom sums (shape-independent bits)
     int lanes = 4;
     int block = 256;
+    bool auto_launch = true;   // lanes and block follow the system's size (until set_launch or the tuner)
     int grid = 0;      // persistent pair-kernel blocks (0: every resident slot), a multiple of 8
     int n_cu = 256;
     int max_lds = 65536;   // LDS bytes one block may allocate
@@ -474,8 +475,35 @@ void build_slices(eamfe_ctx* c)
         }
 }
 
+// Launch shape for the system's size, where the caller has set none.  Lanes
+// per atom: as many as still give at most ten wavefronts per CU (FP64:
+// fourteen).  A small system is bound by the latency of each lane's walk, which
+// more lanes shorten; a large one by the pair work, to which every lane adds
+// its share of loop overhead, row-length spread and lane sums.  Measured, us
+// per call at 1/2/4/8/16 lanes: 4,096 atoms FP32, 100 steps 6024/4122/3072/
+// 2666/2569; 10,976 atoms, 20 steps 1548/1178/922/854/913; 25,512 atoms, one
+// evaluation 116/96/89/89/95; 128,000 atoms, 20 steps 2462/2604/2986/3880/6514;
+// 113,090 atoms FP64, 10 steps 1126/1057/1176/1375/1857; 128 atoms FP64, 100
+// steps 5178/3693/2620/2034/1742.  Threads per block: FP32 512 (the table is
+// staged once for eight wavefronts; 4,096 atoms at 256/512/1024: 2703/2569/
+// 2758), 256 where the chip is filled more than four times over (1.3 million
+// atoms, 4 steps: 2661 against 2806 at 512); FP64 1024 where the tables are
+// staged in LDS (two units per CU and more; 256/512/1024: 1390/1140/1057), else
+// 64 (128 atoms at 64/128/256: 1742/1810/1898).
+void choose_launch(eamfe_ctx* c)
+{
+    const bool f32 = c->precision == EAMFE_FP32;
+    const long most = (f32 ? 10L : 14L) * c->n_cu;
+    int lanes = 16;
+    while (lanes > 1 && (long)c->N * lanes / 64 > most) lanes /= 2;
+    const long waves = (long)c->N * lanes / 64;
+    c->lanes = lanes;
+    c->block = f32 ? (waves > 64L * c->n_cu ? 256 : 512) : (waves >= 2L * c->n_cu ? 1024 : 64);
+}
+
 int build_tiles(eamfe_ctx* c)
 {
+    if (c->auto_launch) choose_launch(c);
     const int A = 64 / c->lanes;
     c->tiles.clear();
     std::vector<std::vector<Tile>> per(c->n_rep);
@@ -1282,6 +1310,7 @@ int eamfe_set_launch(eamfe_ctx* c, int lanes, int block)
         return fail(c, EAMFE_EINVAL, "block_threads must be a multiple of 64 in [64, 1024]");
     if (lanes) c->lanes = lanes;
     if (block) c->block = block;
+    if (lanes || block) c->auto_launch = false;
     if (c->n_rep) {
         (void)hipSetDevice(c->device);
         HIPCHK(c, hipStreamSynchronize(c->stream));
@@ -1858,6 +1887,8 @@ int eamfe_autotune(eamfe_ctx* c, const eamfe_protocol* p, int64_t step, const do
     const int timing = c->timing;
     c->timing = 0;
     const int lanes0 = c->lanes, block0 = c->block, grid0 = c->grid;
+    const bool auto0 = c->auto_launch;
+    c->auto_launch = false;   // the trials set the shape
     int best_l = lanes0, best_b = block0, best_g = grid0;
     double best = 1e300;
     hipEvent_t e0, e1;
@@ -1993,6 +2024,7 @@ done:
     c->lanes = rc ? lanes0 : best_l;
     c->block = rc ? block0 : best_b;
     c->grid = rc ? grid0 : best_g;
+    c->auto_launch = rc && auto0;
     {
         const int r2 = build_tiles(c);
         if (!rc) rc = r2;
