@@ -596,7 +596,9 @@ NeighArgs neigh_args(eamfe_ctx* c, const double4* P)
     a.n_cells = c->n_cells;
     a.ccap = c->ccap;
     a.cap = c->cap;
-    a.chunk = std::max(512, c->ccap);
+    // k_list holds a stream of up to 1024 candidates in registers: a chunk of
+    // that size where its rows leave the LDS for it, 512 at least
+    a.chunk = std::max({512, c->ccap, std::min(1024, kListLds / 16 - c->cap)});
     a.rl2 = (c->r_cut + c->skin) * (c->r_cut + c->skin);
     {
         // candidate test in single precision on folded coordinates: widen the

@@ -181,7 +181,11 @@ struct AdjointArgs {
     int lanes;                  // lanes per atom (set by the launcher)
 };
 
-// LDS of the row builder: the sorted records of up to `atoms` atoms, then its
+// LDS of a block of the global row builder (k_list): four wavefronts, each
+// with a row buffer and a candidate chunk.
+constexpr int kListLds = 64 * 1024;
+
+// LDS of the LDS row builder: the sorted records of up to `atoms` atoms, then its
 // workspace: `cells` + 1 cell starts, the work entries (sorted position and
 // cell; at most one per cell plus two per wavefront) and per wavefront a row
 // buffer of `cap` slots and a chunk of the candidate stream (16-bit

@@ -611,12 +611,15 @@ __device__ __forceinline__ double3 sep(const RepDesc& R, const double4& a, const
 // around the atom's own, so rows have a fixed order.
 // --------------------------------------------------------------------------
 // Prefix sums over the replicas of the global builder (not k_rows_lds) of
-// the atoms and of the cells to rebuild:
-// pre[r] (atoms of flagged replicas before r), pre[n_rep + 1 + r] (cells of
+// the atoms to rebuild and of the row builder's work items (a cell each, or
+// kPairAtoms atoms of a replica with all-pairs rows):
+// pre[r] (atoms of flagged replicas before r), pre[n_rep + 1 + r] (items of
 // flagged replicas before r), totals at index n_rep and 2 n_rep + 1.  One
 // block (any size, multiple of 64); the list kernels take their work items
 // from these, so each of them needs no pass over all atoms or cells.  Every
 // thread returns the number of flagged replicas.
+constexpr int kPairAtoms = 8;
+
 __device__ int flag_prefix(const RepDesc* reps, const int32_t* rebuild, int n_rep, int32_t* pre)
 {
     __shared__ int wa[16], wc[16], wr[16];
@@ -627,7 +630,8 @@ __device__ int flag_prefix(const RepDesc* reps, const int32_t* rebuild, int n_re
         int va = 0, vc = 0;
         if (r < n_rep && rebuild[r] && !reps[r].lds) {   // replicas of the global builder only
             va = reps[r].n;
-            vc = reps[r].nc[0] * reps[r].nc[1] * reps[r].nc[2];
+            vc = reps[r].nc[0] > 0 ? reps[r].nc[0] * reps[r].nc[1] * reps[r].nc[2]
+                                   : (va + kPairAtoms - 1) / kPairAtoms;
         }
         const int xa = wave_scan(va), xc = wave_scan(vc);
         const int nf = __popcll(__ballot(va > 0));   // flagged replicas of this wavefront
@@ -754,22 +758,27 @@ __global__ __launch_bounds__(kBinBlock) void k_bin(NeighArgs a, StepArgs s)
     }
 }
 
-// Rows: one wavefront per atom of a flagged replica (waves of the whole grid
-// stride over the flagged atoms, work items from the prefix).  The 125
-// stencil cells' members form one candidate stream in a fixed order (cells
-// by offset, atoms by id).  The stream is staged in LDS a chunk at a time:
-// each lane copies one cell's members (their loads in flight together) and
-// sorts them (a sorting network of eight, an insertion sort beyond), so the
-// cells need no sorting pass of their own and a candidate costs one LDS read.
-// Each pass tests 64 candidates with exact minimum-image box coordinates and
-// appends the accepted ones in stream order (ballot + prefix count) to a row
-// buffer in LDS, which is written out as whole 16-byte slabs at the end (row
-// stores inside the loop would make every pass's loads wait for them).
+// Rows: one wavefront per cell of a flagged replica (waves of the whole grid
+// stride over the items of the prefix); atoms of one cell share their
+// stencil.  The 125 stencil cells' members form one candidate stream in a
+// fixed order (cells by offset, atoms by id).  It is staged in LDS a chunk at a
+// time: each lane copies one cell's members (their loads in flight together)
+// and sorts them (a sorting network of eight or sixteen, an insertion sort
+// beyond), so the cells need no sorting pass of their own.  A stream that fits
+// one chunk (the usual case) then goes into registers once, up to 16 records
+// per lane, and every atom of the cell is tested against them with exact
+// minimum-image box coordinates; a longer one is staged anew for every atom.
+// Accepted candidates go in stream order (ballot and prefix count) to a row
+// buffer in LDS, written out as whole 16-byte slabs.  Bound by the tests'
+// arithmetic; with a wavefront per atom every atom staged and gathered its
+// 125 cells anew.  All 128,000 atoms of eight replicas, rows of 179: 399 -> 134
+// us; 1.3 million atoms, rows of 77 (2.4 atoms per cell): 2327 -> 1424 us.
 constexpr int kListBlock = 256;
 constexpr int kListGrid = 2048;
 constexpr int kStencil = 125;   // 5 x 5 x 5 cells
+constexpr int kListCand = 16;   // candidates per lane held in registers
 
-__global__ __launch_bounds__(kListBlock) void k_list(NeighArgs a, int n_rep)
+__global__ __launch_bounds__(kListBlock, 4) void k_list(NeighArgs a, int n_rep)
 {
     extern __shared__ int rowbuf[];             // [waves][cap] accepted ids, then [waves][chunk] candidates
     __shared__ int cend[kListBlock / 64][kStencil];   // per wave: inclusive prefix of stencil cell sizes
@@ -779,8 +788,7 @@ __global__ __launch_bounds__(kListBlock) void k_list(NeighArgs a, int n_rep)
     const float rl2 = a.rl2_f;
     int* row = rowbuf + (size_t)w * cap;
     int* cb = rowbuf + (size_t)(kListBlock / 64) * cap + (size_t)w * a.chunk;   // this wave's candidate chunk
-    const int32_t* pre = a.flag_pre;
-    const uint64_t below = (1ull << lw) - 1ull;
+    const int32_t* pre = a.flag_pre + n_rep + 1;
     const int waves = gridDim.x * (kListBlock / 64);
     // the wave's first item: its replica's probes go out with the total's
     // read (the empty asm takes their results before the loop's test, so the
@@ -794,196 +802,255 @@ __global__ __launch_bounds__(kListBlock) void k_list(NeighArgs a, int n_rep)
         int plo = plo0, roff = off0;
         const int lo = f == f0 ? lo0 : item_replica(pre, a.reps, n_rep, f, plo, roff);
         const RepDesc& R = a.reps[lo];
-        const int il = f - plo;
-        const int i = roff + il;
-        // the atom's record and reference position go out with the
-        // replica's fields (the empty asm again keeps the field reads from
-        // sinking into the branches that use them)
-        const uint4 qi = a.Q[i];
-        const double4 pi = a.P[i];   // the list's reference position, read with the record
+        const int il0 = f - plo;   // the item within its replica: a cell, or a group of atoms
         const int rn = R.n, nc0 = R.nc[0], nc1 = R.nc[1], nc2 = R.nc[2], cbase = R.cell_base;
-        const double L0 = R.L[0], L1 = R.L[1], L2 = R.L[2];
-        __asm__ volatile("" : : "v"(rn), "v"(nc0), "v"(nc1), "v"(nc2), "v"(cbase));
-        const float sx = (float)(L0 * 2.3283064365386963e-10), sy = (float)(L1 * 2.3283064365386963e-10),
-                    sz = (float)(L2 * 2.3283064365386963e-10);
+        const float sx = (float)(R.L[0] * 2.3283064365386963e-10), sy = (float)(R.L[1] * 2.3283064365386963e-10),
+                    sz = (float)(R.L[2] * 2.3283064365386963e-10);
         int cnt = 0;
-        auto test = [&](int jl) {
-            const uint4 qj = a.Q[roff + jl];
-            const float dx = (float)(int)(qi.x - qj.x) * sx, dy = (float)(int)(qi.y - qj.y) * sy,
-                        dz = (float)(int)(qi.z - qj.z) * sz;
-            return jl != il && dx * dx + dy * dy + dz * dz < rl2;
-        };
-        auto append = [&](bool acc, int j) {
+        // 64 candidates (local id jl < 0: none) against atom il with record qi:
+        // those in range are appended to the row
+        auto test = [&](const uint4& qi, int il, int jl, uint32_t x, uint32_t y, uint32_t z) {
+            const float dx = (float)(int)(qi.x - x) * sx, dy = (float)(int)(qi.y - y) * sy,
+                        dz = (float)(int)(qi.z - z) * sz;
+            const bool acc = jl >= 0 && jl != il && dx * dx + dy * dy + dz * dz < rl2;
             const uint64_t m = __ballot(acc);
-            const int rank = __popcll(m & below);
-            if (acc && cnt + rank < cap) row[cnt + rank] = j;
+            const int slot = cnt + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                             __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+            if (acc && slot < cap) row[slot] = roff + jl;
             cnt += __popcll(m);
         };
-        if (nc0 == 0) {
-            for (int s0 = 0; s0 < rn; s0 += 64) {
-                const int jl = s0 + lw;
-                append(jl < rn && test(jl), roff + jl);
-            }
-        } else {   // cells
-            const int cx = box_cell(qi.x, nc0), cy = box_cell(qi.y, nc1), cz = box_cell(qi.z, nc2);
-            // lane l holds stencil cells l and 64 + l: both cells' counts are
-            // read together, then prefix-summed in stencil order
-            int n_c[2] = {0, 0}, cc[2] = {0, 0};
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int q = 64 * h + lw;
-                if (q < kStencil) {
-                    const int ux = wrap_cell(cx + q / 25 - 2, nc0);
-                    const int uy = wrap_cell(cy + (q / 5) % 5 - 2, nc1);
-                    const int uz = wrap_cell(cz + q % 5 - 2, nc2);
-                    cc[h] = cbase + (ux * nc1 + uy) * nc2 + uz;
-                    n_c[h] = min(a.cell_cnt[cc[h]], a.ccap);
-                }
-            }
-            int tot_c = 0;   // running total of the stencil cells' sizes
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int q = 64 * h + lw;
-                const int incl = wave_scan(n_c[h]) + tot_c;
-                if (q < kStencil) {
-                    cend[w][q] = incl;
-                    cid[w][q] = cc[h];
-                }
-                tot_c = __builtin_amdgcn_readlane(incl, 63);
-            }
+        // pad the last slab with the atom itself (cap is a multiple of 32), then
+        // write the row as whole slabs
+        auto write = [&](int i) {
             __builtin_amdgcn_wave_barrier();
-            constexpr int U = 4;   // passes per iteration: their independent loads are in flight together
-            int q0 = 0, base = 0;  // first stencil cell of the chunk, candidates before it
-            while (q0 < kStencil) {
-                // the cells (up to 128, two per lane) whose members fit the chunk
-                // (a cell always does: chunk >= ccap)
-                int q1 = q0;
+            const int used = cnt < cap ? cnt : cap;
+            const int pad_end = min((used + 3) & ~3, cap);
+            if (used + lw < pad_end) row[used + lw] = i;
+            __builtin_amdgcn_wave_barrier();
+            for (int b = lw; 4 * b < pad_end; b += 64)
+                *(int4*)(a.nbr + ((size_t)b * (size_t)N + (size_t)i) * 4) =
+                    make_int4(row[4 * b], row[4 * b + 1], row[4 * b + 2], row[4 * b + 3]);
+            if (lw == 0) {
+                if (cnt > cap) atomicOr(a.status, ST_NEIGH_OVERFLOW);
+                a.nnb[i] = used;
+            }
+            __builtin_amdgcn_wave_barrier();   // the row buffer is reused by the next atom
+            cnt = 0;
+        };
+        // the candidates of registers k = 0 .. kListCand - 1, from local ids
+        uint32_t cx_[kListCand], cy_[kListCand], cz_[kListCand];
+        int cj[kListCand];
+        auto load = [&](int n, auto&& id_at) {
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const int qq = q0 + 64 * h + lw;
-                    const int c = __popcll(__ballot(qq < kStencil && cend[w][qq] - base <= a.chunk));
-                    if (q1 == q0 + 64 * h) q1 += c;   // uniform
+            for (int k = 0; k < kListCand; ++k) {
+                cx_[k] = cy_[k] = cz_[k] = 0u;
+                cj[k] = -1;
+                if (64 * k < n) {   // uniform
+                    cj[k] = lw < n - 64 * k ? id_at(64 * k) : -1;
+                    const uint4 q = a.Q[roff + max(cj[k], 0)];
+                    cx_[k] = q.x;
+                    cy_[k] = q.y;
+                    cz_[k] = q.z;
                 }
-                q1 = q1 > q0 ? q1 : q0 + 1;
-                const int end = cend[w][q1 - 1] - base;
-                // lane l stages cells q0 + l and q0 + 64 + l in id order with a
-                // sorting network (Batcher's odd-even merge): eight inputs, or
-                // sixteen when some cell of the wavefront holds more than eight
-                // (a uniform branch), an insertion sort beyond
-                int s0[2], n[2];
-                const int32_t* src[2];
+            }
+        };
+        auto test_regs = [&](const uint4& qi, int il, int n) {
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const int qq = q0 + 64 * h + lw;
-                    const bool mine = qq < q1;
-                    s0[h] = mine ? (qq ? cend[w][qq - 1] : 0) - base : 0;
-                    n[h] = mine ? cend[w][qq] - base - s0[h] : 0;
-                    src[h] = a.cell_atoms + (size_t)(mine ? cid[w][qq] : 0) * a.ccap;
-                }
-                auto cmpx = [](int* v, int p, int r) {
-                    const int lo = min(v[p], v[r]), hi = max(v[p], v[r]);
-                    v[p] = lo;
-                    v[r] = hi;
-                };
-                if (__ballot(n[0] > 8 || n[1] > 8) == 0) {
-                    int m[2][8];   // both cells' loads in flight together
-#pragma unroll
-                    for (int h = 0; h < 2; ++h)
-#pragma unroll
-                        for (int t = 0; t < 8; ++t) m[h][t] = t < n[h] ? src[h][t] : 0x7fffffff;
-#pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        int* v = m[h];
-                        cmpx(v, 0, 1); cmpx(v, 2, 3); cmpx(v, 4, 5); cmpx(v, 6, 7);
-                        cmpx(v, 0, 2); cmpx(v, 1, 3); cmpx(v, 4, 6); cmpx(v, 5, 7);
-                        cmpx(v, 1, 2); cmpx(v, 5, 6);
-                        cmpx(v, 0, 4); cmpx(v, 1, 5); cmpx(v, 2, 6); cmpx(v, 3, 7);
-                        cmpx(v, 2, 4); cmpx(v, 3, 5);
-                        cmpx(v, 1, 2); cmpx(v, 3, 4); cmpx(v, 5, 6);
-#pragma unroll
-                        for (int t = 0; t < 8; ++t)
-                            if (t < n[h]) cb[s0[h] + t] = v[t];
+            for (int k = 0; k < kListCand; ++k)
+                if (64 * k < n) test(qi, il, cj[k], cx_[k], cy_[k], cz_[k]);
+        };
+        // own atoms, up to 64 at a time, one per lane: record and reference position
+        auto rows_of = [&](int count, int own, auto&& one_row) {
+            const int i = roff + own;
+            const uint4 q = a.Q[i];
+            if (lw < count) {
+                const double4 p = a.P[i];
+                a.xref[i] = p.x;
+                a.xref[N + i] = p.y;
+                a.xref[2 * N + i] = p.z;
+            }
+            for (int t = 0; t < count; ++t) {
+                const int il = __builtin_amdgcn_readlane(own, t);
+                const uint4 qi = make_uint4((uint32_t)__builtin_amdgcn_readlane((int)q.x, t),
+                                            (uint32_t)__builtin_amdgcn_readlane((int)q.y, t),
+                                            (uint32_t)__builtin_amdgcn_readlane((int)q.z, t), 0u);
+                one_row(qi, il);
+                write(roff + il);
+            }
+        };
+        if (nc0 == 0) {   // all-pairs rows of a group of atoms: every other atom in id order
+            const int first = il0 * kPairAtoms, count = min(kPairAtoms, rn - first);
+            const int own = min(first + lw, rn - 1);
+            if (rn <= 64 * kListCand) {
+                load(rn, [&](int k) { return k + lw; });
+                rows_of(count, own, [&](const uint4& qi, int il) { test_regs(qi, il, rn); });
+            } else {
+                rows_of(count, own, [&](const uint4& qi, int il) {
+                    for (int s0 = 0; s0 < rn; s0 += 64) {
+                        const int jl = s0 + lw < rn ? s0 + lw : -1;
+                        const uint4 q = a.Q[roff + max(jl, 0)];
+                        test(qi, il, jl, q.x, q.y, q.z);
                     }
-                } else {
+                });
+            }
+            continue;
+        }
+        const int cz = il0 % nc2, cy = (il0 / nc2) % nc1, cx = il0 / (nc1 * nc2);
+        // lane l holds stencil cells l and 64 + l: both cells' counts are
+        // read together, then prefix-summed in stencil order
+        int n_c[2] = {0, 0}, cc[2] = {0, 0};
 #pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        int v[16];
+        for (int h = 0; h < 2; ++h) {
+            const int q = 64 * h + lw;
+            if (q < kStencil) {
+                const int ux = wrap_cell(cx + q / 25 - 2, nc0);
+                const int uy = wrap_cell(cy + (q / 5) % 5 - 2, nc1);
+                const int uz = wrap_cell(cz + q % 5 - 2, nc2);
+                cc[h] = cbase + (ux * nc1 + uy) * nc2 + uz;
+                n_c[h] = min(a.cell_cnt[cc[h]], a.ccap);
+            }
+        }
+        constexpr int kOwn = kStencil / 2;   // the cell itself
+        const int members = __builtin_amdgcn_readlane(n_c[0], kOwn);
+        if (members == 0) continue;
+        int tot_c = 0;   // running total of the stencil cells' sizes
 #pragma unroll
-                        for (int t = 0; t < 16; ++t) v[t] = t < n[h] ? src[h][t] : 0x7fffffff;
-                        cmpx(v, 0, 1); cmpx(v, 2, 3); cmpx(v, 0, 2); cmpx(v, 1, 3); cmpx(v, 1, 2);
-                        cmpx(v, 4, 5); cmpx(v, 6, 7); cmpx(v, 4, 6); cmpx(v, 5, 7); cmpx(v, 5, 6);
-                        cmpx(v, 0, 4); cmpx(v, 2, 6); cmpx(v, 2, 4); cmpx(v, 1, 5); cmpx(v, 3, 7);
-                        cmpx(v, 3, 5); cmpx(v, 1, 2); cmpx(v, 3, 4); cmpx(v, 5, 6); cmpx(v, 8, 9);
-                        cmpx(v, 10, 11); cmpx(v, 8, 10); cmpx(v, 9, 11); cmpx(v, 9, 10); cmpx(v, 12, 13);
-                        cmpx(v, 14, 15); cmpx(v, 12, 14); cmpx(v, 13, 15); cmpx(v, 13, 14); cmpx(v, 8, 12);
-                        cmpx(v, 10, 14); cmpx(v, 10, 12); cmpx(v, 9, 13); cmpx(v, 11, 15); cmpx(v, 11, 13);
-                        cmpx(v, 9, 10); cmpx(v, 11, 12); cmpx(v, 13, 14); cmpx(v, 0, 8); cmpx(v, 4, 12);
-                        cmpx(v, 4, 8); cmpx(v, 2, 10); cmpx(v, 6, 14); cmpx(v, 6, 10); cmpx(v, 2, 4);
-                        cmpx(v, 6, 8); cmpx(v, 10, 12); cmpx(v, 1, 9); cmpx(v, 5, 13); cmpx(v, 5, 9);
-                        cmpx(v, 3, 11); cmpx(v, 7, 15); cmpx(v, 7, 11); cmpx(v, 3, 5); cmpx(v, 7, 9);
-                        cmpx(v, 11, 13); cmpx(v, 1, 2); cmpx(v, 3, 4); cmpx(v, 5, 6); cmpx(v, 7, 8);
-                        cmpx(v, 9, 10); cmpx(v, 11, 12); cmpx(v, 13, 14);
+        for (int h = 0; h < 2; ++h) {
+            const int q = 64 * h + lw;
+            const int incl = wave_scan(n_c[h]) + tot_c;
+            if (q < kStencil) {
+                cend[w][q] = incl;
+                cid[w][q] = cc[h];
+            }
+            tot_c = __builtin_amdgcn_readlane(incl, 63);
+        }
+        __builtin_amdgcn_wave_barrier();
+        // stages the stream from stencil cell q0 on (`base` candidates before
+        // it); returns its length, and the next cell in q1
+        auto stage = [&](int q0, int base, int& q1) {
+            // the cells (up to 128, two per lane) whose members fit the chunk
+            // (a cell always does: chunk >= ccap)
+            __builtin_amdgcn_wave_barrier();
+            q1 = q0;
 #pragma unroll
-                        for (int t = 0; t < 16; ++t)
-                            if (t < n[h]) cb[s0[h] + t] = v[t];
-                        if (n[h] > 16) {   // the rest in, then an insertion sort of the whole cell
-                            for (int t = 16; t < n[h]; ++t) cb[s0[h] + t] = src[h][t];
-                            for (int t = 1; t < n[h]; ++t) {
-                                const int x = cb[s0[h] + t];
-                                int u = t;
-                                while (u > 0 && cb[s0[h] + u - 1] > x) {
-                                    cb[s0[h] + u] = cb[s0[h] + u - 1];
-                                    --u;
-                                }
-                                cb[s0[h] + u] = x;
+            for (int h = 0; h < 2; ++h) {
+                const int qq = q0 + 64 * h + lw;
+                const int c = __popcll(__ballot(qq < kStencil && cend[w][qq] - base <= a.chunk));
+                if (q1 == q0 + 64 * h) q1 += c;   // uniform
+            }
+            q1 = q1 > q0 ? q1 : q0 + 1;
+            const int end = cend[w][q1 - 1] - base;
+            // lane l stages cells q0 + l and q0 + 64 + l in id order with a
+            // sorting network (Batcher's odd-even merge): eight inputs, or
+            // sixteen when some cell of the wavefront holds more than eight
+            // (a uniform branch), an insertion sort beyond
+            int s0[2], n[2];
+            const int32_t* src[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int qq = q0 + 64 * h + lw;
+                const bool mine = qq < q1;
+                s0[h] = mine ? (qq ? cend[w][qq - 1] : 0) - base : 0;
+                n[h] = mine ? cend[w][qq] - base - s0[h] : 0;
+                src[h] = a.cell_atoms + (size_t)(mine ? cid[w][qq] : 0) * a.ccap;
+            }
+            auto cmpx = [](int* v, int p, int r) {
+                const int lo = min(v[p], v[r]), hi = max(v[p], v[r]);
+                v[p] = lo;
+                v[r] = hi;
+            };
+            if (__ballot(n[0] > 8 || n[1] > 8) == 0) {
+                int m[2][8];   // both cells' loads in flight together
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int t = 0; t < 8; ++t) m[h][t] = t < n[h] ? src[h][t] : 0x7fffffff;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    int* v = m[h];
+                    cmpx(v, 0, 1); cmpx(v, 2, 3); cmpx(v, 4, 5); cmpx(v, 6, 7);
+                    cmpx(v, 0, 2); cmpx(v, 1, 3); cmpx(v, 4, 6); cmpx(v, 5, 7);
+                    cmpx(v, 1, 2); cmpx(v, 5, 6);
+                    cmpx(v, 0, 4); cmpx(v, 1, 5); cmpx(v, 2, 6); cmpx(v, 3, 7);
+                    cmpx(v, 2, 4); cmpx(v, 3, 5);
+                    cmpx(v, 1, 2); cmpx(v, 3, 4); cmpx(v, 5, 6);
+#pragma unroll
+                    for (int t = 0; t < 8; ++t)
+                        if (t < n[h]) cb[s0[h] + t] = v[t];
+                }
+            } else {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    int v[16];
+#pragma unroll
+                    for (int t = 0; t < 16; ++t) v[t] = t < n[h] ? src[h][t] : 0x7fffffff;
+                    cmpx(v, 0, 1); cmpx(v, 2, 3); cmpx(v, 0, 2); cmpx(v, 1, 3); cmpx(v, 1, 2);
+                    cmpx(v, 4, 5); cmpx(v, 6, 7); cmpx(v, 4, 6); cmpx(v, 5, 7); cmpx(v, 5, 6);
+                    cmpx(v, 0, 4); cmpx(v, 2, 6); cmpx(v, 2, 4); cmpx(v, 1, 5); cmpx(v, 3, 7);
+                    cmpx(v, 3, 5); cmpx(v, 1, 2); cmpx(v, 3, 4); cmpx(v, 5, 6); cmpx(v, 8, 9);
+                    cmpx(v, 10, 11); cmpx(v, 8, 10); cmpx(v, 9, 11); cmpx(v, 9, 10); cmpx(v, 12, 13);
+                    cmpx(v, 14, 15); cmpx(v, 12, 14); cmpx(v, 13, 15); cmpx(v, 13, 14); cmpx(v, 8, 12);
+                    cmpx(v, 10, 14); cmpx(v, 10, 12); cmpx(v, 9, 13); cmpx(v, 11, 15); cmpx(v, 11, 13);
+                    cmpx(v, 9, 10); cmpx(v, 11, 12); cmpx(v, 13, 14); cmpx(v, 0, 8); cmpx(v, 4, 12);
+                    cmpx(v, 4, 8); cmpx(v, 2, 10); cmpx(v, 6, 14); cmpx(v, 6, 10); cmpx(v, 2, 4);
+                    cmpx(v, 6, 8); cmpx(v, 10, 12); cmpx(v, 1, 9); cmpx(v, 5, 13); cmpx(v, 5, 9);
+                    cmpx(v, 3, 11); cmpx(v, 7, 15); cmpx(v, 7, 11); cmpx(v, 3, 5); cmpx(v, 7, 9);
+                    cmpx(v, 11, 13); cmpx(v, 1, 2); cmpx(v, 3, 4); cmpx(v, 5, 6); cmpx(v, 7, 8);
+                    cmpx(v, 9, 10); cmpx(v, 11, 12); cmpx(v, 13, 14);
+#pragma unroll
+                    for (int t = 0; t < 16; ++t)
+                        if (t < n[h]) cb[s0[h] + t] = v[t];
+                    if (n[h] > 16) {   // the rest in, then an insertion sort of the whole cell
+                        for (int t = 16; t < n[h]; ++t) cb[s0[h] + t] = src[h][t];
+                        for (int t = 1; t < n[h]; ++t) {
+                            const int x = cb[s0[h] + t];
+                            int u = t;
+                            while (u > 0 && cb[s0[h] + u - 1] > x) {
+                                cb[s0[h] + u] = cb[s0[h] + u - 1];
+                                --u;
                             }
+                            cb[s0[h] + u] = x;
                         }
                     }
                 }
-                __builtin_amdgcn_wave_barrier();
-                for (int k0 = 0; k0 < end; k0 += 64 * U) {
-                    int jl[U];
-                    uint4 qj[U];
+            }
+            __builtin_amdgcn_wave_barrier();
+            return end;
+        };
+        int q1;
+        if (tot_c <= min(64 * kListCand, a.chunk)) {   // one chunk: the stream in registers
+            stage(0, 0, q1);
+            const int own0 = cend[w][kOwn - 1];
+            load(tot_c, [&](int k) { return cb[k + lw]; });
+            for (int g = 0; g < members; g += 64) {
+                const int count = min(64, members - g);
+                const int own = cb[own0 + g + min(lw, count - 1)];
+                rows_of(count, own, [&](const uint4& qi, int il) { test_regs(qi, il, tot_c); });
+            }
+        } else {
+            for (int g = 0; g < members; g += 64) {
+                const int count = min(64, members - g);
+                stage(kOwn, cend[w][kOwn - 1], q1);   // the cell's own members in id order
+                const int own = cb[g + min(lw, count - 1)];
+                rows_of(count, own, [&](const uint4& qi, int il) {
+                    for (int q0 = 0, base = 0; q0 < kStencil;) {
+                        const int end = stage(q0, base, q1);
+                        for (int k0 = 0; k0 < end; k0 += 64 * 4) {   // four reads in flight
+                            int jl[4];
+                            uint4 qj[4];
 #pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        const int k = k0 + 64 * u + lw;
-                        jl[u] = k < end ? cb[k] : -1;
+                            for (int u = 0; u < 4; ++u) jl[u] = k0 + 64 * u + lw < end ? cb[k0 + 64 * u + lw] : -1;
+#pragma unroll
+                            for (int u = 0; u < 4; ++u) qj[u] = a.Q[roff + max(jl[u], 0)];
+#pragma unroll
+                            for (int u = 0; u < 4; ++u) test(qi, il, jl[u], qj[u].x, qj[u].y, qj[u].z);
+                        }
+                        base = cend[w][q1 - 1];
+                        q0 = q1;
                     }
-#pragma unroll
-                    for (int u = 0; u < U; ++u) qj[u] = a.Q[roff + (jl[u] < 0 ? il : jl[u])];
-#pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        const float dx = (float)(int)(qi.x - qj[u].x) * sx, dy = (float)(int)(qi.y - qj[u].y) * sy,
-                                    dz = (float)(int)(qi.z - qj[u].z) * sz;
-                        const bool acc = jl[u] >= 0 && jl[u] != il && dx * dx + dy * dy + dz * dz < rl2;
-                        append(acc, roff + jl[u]);
-                    }
-                }
-                __builtin_amdgcn_wave_barrier();   // the chunk is refilled next
-                base = cend[w][q1 - 1];
-                q0 = q1;
+                });
             }
         }
-        // pad the last slab with the atom itself (cap is a multiple of 32), then
-        // write the row as whole slabs
-        const int used = cnt < cap ? cnt : cap;
-        const int pad_end = min((used + 3) & ~3, cap);
-        if (used + lw < pad_end) row[used + lw] = i;
-        __builtin_amdgcn_wave_barrier();
-        for (int b = lw; 4 * b < pad_end; b += 64)
-            *(int4*)(a.nbr + ((size_t)b * (size_t)N + (size_t)i) * 4) =
-                make_int4(row[4 * b], row[4 * b + 1], row[4 * b + 2], row[4 * b + 3]);
-        if (lw == 0) {
-            if (cnt > cap) {
-                atomicOr(a.status, ST_NEIGH_OVERFLOW);
-                cnt = cap;
-            }
-            a.nnb[i] = cnt;
-            a.xref[i] = pi.x;
-            a.xref[N + i] = pi.y;
-            a.xref[2 * N + i] = pi.z;
-        }
-        __builtin_amdgcn_wave_barrier();   // the row buffer is reused by the next atom
     }
 }
 
@@ -2053,7 +2120,7 @@ int launch_neigh_rebuild(const NeighArgs& a, const StepArgs& st, int lanes, int 
         hipLaunchKernelGGL(k_bin, dim3(bin_blocks), dim3(kBinBlock), 0, s, a, st);
         // one row buffer and one candidate chunk per wavefront
         const size_t lds = (size_t)((kListBlock / 64) * (a.cap + a.chunk)) * sizeof(int);
-        if (lds > 64 * 1024) return (int)hipErrorInvalidValue;
+        if (lds > (size_t)kListLds) return (int)hipErrorInvalidValue;
         hipLaunchKernelGGL(k_list, dim3(kListGrid), dim3(kListBlock), lds, s, a, a.n_rep);
     }
     if (a.n_lds > 0) {
