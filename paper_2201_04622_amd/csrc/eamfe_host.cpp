@@ -62,6 +62,12 @@ struct Shape {
     long n_r = 0, n_rho = 0;
     long cap = 0, n_cells = 0, ccap = 0;
     long lam_len = 0;      // entries of the lambda table
+
+    bool operator==(const Shape& o) const
+    {
+        return N == o.N && n_rep == o.n_rep && max_units == o.max_units && max_slices == o.max_slices && n_r == o.n_r &&
+               n_rho == o.n_rho && cap == o.cap && n_cells == o.n_cells && ccap == o.ccap && lam_len == o.lam_len;
+    }
 };
 
 // Buffer groups of the arena, in layout order.  A group that changes size
@@ -104,6 +110,13 @@ struct eamfe_ctx {
     std::vector<int4> slices;  // per block of a staged pair launch: first unit, units, replica's first atom, atoms
     int max_rep_atoms = 0;
     DevBuf slices_d;
+    // pinned host memory: what crosses to or from the device in a call goes
+    // through it, so that a call waits for the stream once (pageable copies wait
+    // each on their own).  First kPinHead bytes: status word, adjoint weights;
+    // the rest: tables on their way up
+    char* pin = nullptr;
+    size_t pin_bytes = 0;
+    int last_status = -1;   // status read by the last chunk of run_range (-1: none)
     DevBuf reps_d, tiles_d, rep_of_d, x0_d, xref_d, Pa_d, Pb_d, Qa_d, Qb_d, e_emb_d, xi_d;
     DevBuf noise_part_d, energy_part_d, U_rep_d, W_state_d;
     DevBuf iter_d, rebuild_d, flag_pre_d, status_d, row_acc_d, msd_d, kscale_d, vir_d, mu_d;
@@ -113,11 +126,12 @@ struct eamfe_ctx {
     bool have_list = false;
     double skin = 0.3;
     int cap = 0, ccap = 0, n_cells = 0;
-    DevBuf nbr_d, nnb_d, cell_cnt_d, cell_atoms_d, cell_rep_d;
+    DevBuf nbr_d, nnb_d, cell_cnt_d, cell_atoms_d;
     // rows of replicas that fit one block's LDS come from k_rows_lds
     int lds_rows = 1;                       // 0: every replica through k_bin / k_list
     int n_lds = 0, n_global = 0, lds_atoms = 0, lds_cells = 0, lds_waves = 0;
     DevBuf lds_list_d;                      // [n_rep] those replicas, in order
+    std::vector<int32_t> lds_list_h;        // as uploaded
 
     // graph replay of the middle iterations (0 = eager launches)
     int graph_iters = 0;
@@ -206,6 +220,20 @@ int fail(eamfe_ctx* c, int code, const std::string& msg)
     } while (0)
 
 constexpr size_t kAlign = 256;
+constexpr size_t kPinHead = 4096;
+
+// Pinned staging of at least `bytes` (the stream has been synchronised since
+// its last use when it has to grow).
+int pin_reserve(eamfe_ctx* c, size_t bytes)
+{
+    if (bytes <= c->pin_bytes) return EAMFE_OK;
+    void* p = nullptr;
+    HIPCHK(c, hipHostMalloc(&p, bytes, hipHostMallocDefault));
+    if (c->pin) (void)hipHostFree(c->pin);
+    c->pin = (char*)p;
+    c->pin_bytes = bytes;
+    return EAMFE_OK;
+}
 
 size_t align_up(size_t b) { return (b + kAlign - 1) / kAlign * kAlign; }
 
@@ -268,7 +296,6 @@ void for_regions(eamfe_ctx* c, const Shape& s, F&& f)
         f(c->nnb_d, G_LIST, N * sizeof(int32_t));
         f(c->cell_cnt_d, G_LIST, nc * sizeof(int32_t));
         f(c->cell_atoms_d, G_LIST, nc * (size_t)s.ccap * sizeof(int32_t));
-        f(c->cell_rep_d, G_LIST, nc * sizeof(int32_t));
     }
     if (s.lam_len) f(c->lam_d, G_LAM, (size_t)s.lam_len * d);
     if (N && s.n_r) {
@@ -297,7 +324,12 @@ void drop_graphs(eamfe_ctx* c);     // below
 int bind(eamfe_ctx* c, const Shape& s)
 {
     const size_t need = layout_bytes(c, s);
+    if (c->arena && s == c->shape && need <= c->arena_bytes) {   // nothing moves
+        c->need = 0;
+        return EAMFE_OK;
+    }
     HIPCHK(c, hipStreamSynchronize(c->stream));   // no pass in flight uses the old layout
+    c->lds_list_h.clear();                        // (the list group may move: uploaded again)
     if (need > c->arena_bytes) {
         if (c->caller_ws || c->no_alloc) {
             c->need = need;
@@ -351,29 +383,42 @@ int bind(eamfe_ctx* c, const Shape& s)
 }
 
 
-// Natural cubic spline on x_k = k h through y[0..n-1] -> [n-1][4] (a, b, c, d)
+// Natural cubic splines on x_k = k h through y[0..n-1] -> [n-1][4] (a, b, c, d)
 // with s(t) = a + t(b + t(c + t d)) on interval m, t = x/h - m.  The second
 // derivatives solve the tridiagonal system M_{k-1} + 4 M_k + M_{k+1} =
 // 6 (y_{k+1} - 2 y_k + y_{k-1}) / h^2 with M_0 = M_{n-1} = 0 (natural ends).
-std::vector<double> natural_spline(const double* y, int n, double h)
+// `count` functions on grids of the same n share the pivots, and their
+// recurrences, each a serial chain, run side by side.
+void natural_splines(int count, const double* const* y, const double* h, int n, std::vector<double>* const* out)
 {
-    std::vector<double> M(n, 0.0), diag(n, 4.0), rhs(n, 0.0);
-    for (int k = 1; k < n - 1; ++k) rhs[k] = 6.0 * (y[k + 1] - 2.0 * y[k] + y[k - 1]) / (h * h);
+    constexpr int kMost = 3;
+    std::vector<double> w(n, 0.0), diag(n, 4.0);
+    std::vector<double> M[kMost], rhs[kMost];
+    for (int f = 0; f < count; ++f) {
+        M[f].assign(n, 0.0);
+        rhs[f].assign(n, 0.0);
+        for (int k = 1; k < n - 1; ++k) rhs[f][k] = 6.0 * (y[f][k + 1] - 2.0 * y[f][k] + y[f][k - 1]) / (h[f] * h[f]);
+    }
     // forward elimination (unit off-diagonals)
     for (int k = 2; k < n - 1; ++k) {
-        const double w = 1.0 / diag[k - 1];
-        diag[k] -= w;
-        rhs[k] -= w * rhs[k - 1];
+        w[k] = 1.0 / diag[k - 1];
+        diag[k] -= w[k];
     }
-    for (int k = n - 2; k >= 1; --k) M[k] = (rhs[k] - (k + 1 < n - 1 ? M[k + 1] : 0.0)) / diag[k];
-    std::vector<double> c(4 * (size_t)(n - 1));
-    for (int m = 0; m < n - 1; ++m) {
-        c[4 * m + 0] = y[m];
-        c[4 * m + 1] = (y[m + 1] - y[m]) - h * h * (2.0 * M[m] + M[m + 1]) / 6.0;
-        c[4 * m + 2] = 0.5 * h * h * M[m];
-        c[4 * m + 3] = h * h * (M[m + 1] - M[m]) / 6.0;
+    for (int k = 2; k < n - 1; ++k)
+        for (int f = 0; f < count; ++f) rhs[f][k] -= w[k] * rhs[f][k - 1];
+    for (int k = n - 2; k >= 1; --k)
+        for (int f = 0; f < count; ++f) M[f][k] = (rhs[f][k] - (k + 1 < n - 1 ? M[f][k + 1] : 0.0)) / diag[k];
+    for (int f = 0; f < count; ++f) {
+        std::vector<double>& c = *out[f];
+        const double hh = h[f];
+        c.resize(4 * (size_t)(n - 1));
+        for (int m = 0; m < n - 1; ++m) {
+            c[4 * m + 0] = y[f][m];
+            c[4 * m + 1] = (y[f][m + 1] - y[f][m]) - hh * hh * (2.0 * M[f][m] + M[f][m + 1]) / 6.0;
+            c[4 * m + 2] = 0.5 * hh * hh * M[f][m];
+            c[4 * m + 3] = hh * hh * (M[f][m + 1] - M[f][m]) / 6.0;
+        }
     }
-    return c;
 }
 
 template <typename real>
@@ -381,7 +426,12 @@ int upload_tables_t(eamfe_ctx* c)
 {
     const int mr = c->n_r - 1, mf = c->n_rho - 1;
     const double inv_h = (c->n_r - 1) / c->r_cut;
-    std::vector<real> pair(8 * (size_t)mr), rho(4 * (size_t)mr), F(4 * (size_t)mf);
+    const size_t bp = 8 * (size_t)mr * sizeof(real), br = 4 * (size_t)mr * sizeof(real),
+                 bf = 4 * (size_t)mf * sizeof(real);
+    OK(pin_reserve(c, kPinHead + bp + br + bf));   // (every caller has synchronised the stream)
+    real* const pair = (real*)(c->pin + kPinHead);
+    real* const rho = pair + 8 * (size_t)mr;
+    real* const F = rho + 4 * (size_t)mr;
     for (int m = 0; m < mr; ++m) {
         for (int q = 0; q < 4; ++q) pair[8 * m + q] = (real)c->c_phi[4 * m + q];
         pair[8 * m + 4] = (real)(c->c_rho[4 * m + 1] * inv_h);
@@ -392,9 +442,10 @@ int upload_tables_t(eamfe_ctx* c)
     }
     for (int m = 0; m < mf; ++m)
         for (int q = 0; q < 4; ++q) F[4 * m + q] = (real)c->c_F[4 * m + q];
-    HIPCHK(c, hipMemcpy(c->tab_pair.p, pair.data(), pair.size() * sizeof(real), hipMemcpyHostToDevice));
-    HIPCHK(c, hipMemcpy(c->tab_rho.p, rho.data(), rho.size() * sizeof(real), hipMemcpyHostToDevice));
-    HIPCHK(c, hipMemcpy(c->tab_F.p, F.data(), F.size() * sizeof(real), hipMemcpyHostToDevice));
+    HIPCHK(c, hipMemcpyAsync(c->tab_pair.p, pair, bp, hipMemcpyHostToDevice, c->stream));
+    HIPCHK(c, hipMemcpyAsync(c->tab_rho.p, rho, br, hipMemcpyHostToDevice, c->stream));
+    HIPCHK(c, hipMemcpyAsync(c->tab_F.p, F, bf, hipMemcpyHostToDevice, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));   // (the caller may go on on another stream)
     return EAMFE_OK;
 }
 
@@ -580,7 +631,6 @@ NeighArgs neigh_args(eamfe_ctx* c, const double4* P)
     a.tiles = (const Tile*)c->tiles_d.p;
     a.reps = (const RepDesc*)c->reps_d.p;
     a.rep_of = (const int32_t*)c->rep_of_d.p;
-    a.cell_rep = (const int32_t*)c->cell_rep_d.p;
     a.P = P;
     a.Q = Q_of(c, P);
     a.n_rep = c->n_rep;
@@ -675,7 +725,6 @@ int plan_lists(eamfe_ctx* c, double skin, int max_neighbors)
     const double rl = c->r_cut + skin;
     double dens_max = 0.0, cellvol_max = 0.0;
     int n_cells = 0;
-    std::vector<int32_t> cell_rep;
     std::vector<RepDesc> reps = c->reps;
     for (int r = 0; r < c->n_rep; ++r) {
         const RepDesc& R = reps[r];
@@ -691,7 +740,6 @@ int plan_lists(eamfe_ctx* c, double skin, int max_neighbors)
     auto classify = [&](bool allow_lds) {
         dens_max = cellvol_max = 0.0;
         n_cells = 0;
-        cell_rep.clear();
         for (int r = 0; r < c->n_rep; ++r) {
             RepDesc& R = reps[r];
             const double V = R.L[0] * R.L[1] * R.L[2];
@@ -707,7 +755,6 @@ int plan_lists(eamfe_ctx* c, double skin, int max_neighbors)
             R.cell_base = n_cells;
             if (cells && !R.lds) {
                 const int k = nc[0] * nc[1] * nc[2];
-                for (int q = 0; q < k; ++q) cell_rep.push_back(r);
                 n_cells += k;
                 cellvol_max = std::max(cellvol_max, V / k * (R.n / V));
             }
@@ -755,9 +802,13 @@ int plan_lists(eamfe_ctx* c, double skin, int max_neighbors)
     c->lds_atoms = lds_atoms;
     c->lds_cells = lds_cells;
     c->lds_waves = lds_waves;
-    if (!lds_list.empty())
-        HIPCHK(c, hipMemcpy(c->lds_list_d.p, lds_list.data(), lds_list.size() * sizeof(int32_t),
-                            hipMemcpyHostToDevice));
+    drop_graphs(c);   // captured launches hold the old skin and builders
+    if (lds_list != c->lds_list_h) {   // (the copy is waited for with the replicas' below)
+        c->lds_list_h = lds_list;
+        if (!lds_list.empty())
+            HIPCHK(c, hipMemcpyAsync(c->lds_list_d.p, lds_list.data(), lds_list.size() * sizeof(int32_t),
+                                     hipMemcpyHostToDevice, c->stream));
+    }
     c->reps = reps;
     c->ccap = ccap;
     c->cap = cap;
@@ -765,9 +816,6 @@ int plan_lists(eamfe_ctx* c, double skin, int max_neighbors)
     c->skin = skin;
     HIPCHK(c, hipMemsetAsync(c->cell_cnt_d.p, 0, (size_t)std::max(1, n_cells) * sizeof(int32_t), c->stream));
     HIPCHK(c, hipMemsetAsync(c->nnb_d.p, 0, (size_t)c->N * sizeof(int32_t), c->stream));
-    if (n_cells)
-        HIPCHK(c, hipMemcpy(c->cell_rep_d.p, cell_rep.data(), cell_rep.size() * sizeof(int32_t),
-                            hipMemcpyHostToDevice));
     OK(upload_reps(c));
     return EAMFE_OK;
 }
@@ -791,12 +839,22 @@ int status_code(int st)
     return EAMFE_OK;
 }
 
-int read_status(eamfe_ctx* c)
+// Waits for the stream and returns the latched status (not cleared).
+int fetch_status(eamfe_ctx* c, int* st)
 {
+    *st = 0;
+    if (c->status_d.p) {   // else no device state yet
+        OK(pin_reserve(c, kPinHead));
+        HIPCHK(c, hipMemcpyAsync(c->pin, c->status_d.p, sizeof(int), hipMemcpyDeviceToHost, c->stream));
+    }
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    if (!c->status_d.p) return EAMFE_OK;   // no device state yet
-    int st = 0;
-    HIPCHK(c, hipMemcpy(&st, c->status_d.p, sizeof(int), hipMemcpyDeviceToHost));
+    if (c->status_d.p) std::memcpy(st, c->pin, sizeof(int));
+    return EAMFE_OK;
+}
+
+// The status st (just fetched) as the call's result; latched conditions are cleared.
+int report_status(eamfe_ctx* c, int st)
+{
     if (st) {
         HIPCHK(c, hipMemset(c->status_d.p, 0, sizeof(int)));
         const int code = status_code(st);
@@ -807,6 +865,13 @@ int read_status(eamfe_ctx* c)
         return fail(c, code, what);
     }
     return EAMFE_OK;
+}
+
+int read_status(eamfe_ctx* c)
+{
+    int st = 0;
+    OK(fetch_status(c, &st));
+    return report_status(c, st);
 }
 
 __global__ void k_set_i64(int64_t* p, int64_t v) { *p = v; }
@@ -949,9 +1014,15 @@ int adjoint_at(eamfe_ctx* c, const double4* P, const double* w_host, int reduce,
     const size_t bins = (size_t)c->n_rep * 3 * nb * 4;
     const double* wd = nullptr;
     if (w_host) {
-        HIPCHK(c, hipMemcpyAsync(c->adj_w_d.p, w_host, (size_t)c->n_rep * sizeof(double), hipMemcpyHostToDevice,
-                                 c->stream));
-        HIPCHK(c, hipStreamSynchronize(c->stream));   // the host array may go away
+        const size_t wb = (size_t)c->n_rep * sizeof(double);
+        OK(pin_reserve(c, kPinHead));
+        if (wb <= kPinHead - kAlign) {   // through the staging: samples of one run write the same weights there
+            std::memcpy(c->pin + kAlign, w_host, wb);
+            HIPCHK(c, hipMemcpyAsync(c->adj_w_d.p, c->pin + kAlign, wb, hipMemcpyHostToDevice, c->stream));
+        } else {
+            HIPCHK(c, hipMemcpyAsync(c->adj_w_d.p, w_host, wb, hipMemcpyHostToDevice, c->stream));
+            HIPCHK(c, hipStreamSynchronize(c->stream));   // the host array may go away
+        }
         wd = (const double*)c->adj_w_d.p;
     }
     LCHK(c, launch_fill_u64(bins_p, bins, 0ull, c->stream));   // a fill kernel: capturable, unlike a memset
@@ -1240,6 +1311,7 @@ int eamfe_destroy(eamfe_ctx* c)
     if (c->ev_graph) (void)hipEventDestroy(c->ev_graph);
     if (c->gstream) (void)hipStreamDestroy(c->gstream);
     if (c->arena && !c->caller_ws) (void)hipFree(c->arena);   // never the caller's workspace
+    if (c->pin) (void)hipHostFree(c->pin);
     delete c;
     return EAMFE_OK;
 }
@@ -1420,9 +1492,11 @@ int eam_setup(eamfe_ctx* c, int n_r, double r_cut, const double* phi, const doub
     c->knots_phi.assign(phi, phi + n_r);
     c->knots_rho.assign(rho, rho + n_r);
     c->knots_F.assign(F, F + n_rho);
-    c->c_phi = natural_spline(phi, n_r, r_cut / (n_r - 1));
-    c->c_rho = natural_spline(rho, n_r, r_cut / (n_r - 1));
-    c->c_F = natural_spline(F, n_rho, rho_max / (n_rho - 1));
+    const double* ys[3] = {phi, rho, F};
+    const double hs[3] = {r_cut / (n_r - 1), r_cut / (n_r - 1), rho_max / (n_rho - 1)};
+    std::vector<double>* cs[3] = {&c->c_phi, &c->c_rho, &c->c_F};
+    natural_splines(n_r == n_rho ? 3 : 2, ys, hs, n_r, cs);
+    if (n_r != n_rho) natural_splines(1, ys + 2, hs + 2, n_rho, cs + 2);
     OK(upload_tables(c));
     c->have_pot = true;
     c->have_list = false;   // the cutoff may have changed
@@ -1526,10 +1600,9 @@ int neigh_build(eamfe_ctx* c, const double* x, double skin, int max_neighbors)
         }
         if (max_neighbors > 0 || attempt >= 6) break;
         // automatic capacity: enlarge rows or bins until this configuration fits
-        HIPCHK(c, hipStreamSynchronize(c->stream));
         int st = 0;
-        HIPCHK(c, hipMemcpy(&st, c->status_d.p, sizeof(int), hipMemcpyDeviceToHost));
-        if (!(st & (ST_NEIGH_OVERFLOW | ST_CELL_OVERFLOW))) break;
+        OK(fetch_status(c, &st));
+        if (!(st & (ST_NEIGH_OVERFLOW | ST_CELL_OVERFLOW))) return report_status(c, st);
         HIPCHK(c, hipMemset(c->status_d.p, 0, sizeof(int)));
         OK(grow_lists(c, st));
     }
@@ -1560,20 +1633,18 @@ int eam_forces(eamfe_ctx* c, const double* x, double* f, double* U, double* e_at
         LCHK(c, launch_density(a, c->precision, c->lanes, c->block, c->stream));
         LCHK(c, launch_force(a, c->precision, c->lanes, c->block, c->stream));
         LCHK(c, launch_finish(a, c->stream));
-        HIPCHK(c, hipStreamSynchronize(c->stream));
+        if (U)
+            HIPCHK(c, hipMemcpy2DAsync(U, sizeof(double), c->U_rep_d.p, 2 * sizeof(double), sizeof(double), c->n_rep,
+                                       hipMemcpyDeviceToDevice, c->stream));
         int st = 0;
-        HIPCHK(c, hipMemcpy(&st, c->status_d.p, sizeof(int), hipMemcpyDeviceToHost));
-        if (!(st & (ST_NEIGH_OVERFLOW | ST_CELL_OVERFLOW)) || attempt >= 6) break;
+        OK(fetch_status(c, &st));
+        if (!(st & (ST_NEIGH_OVERFLOW | ST_CELL_OVERFLOW)) || attempt >= 6) return report_status(c, st);
         // rows or bins too small for this configuration: enlarge and evaluate again
         HIPCHK(c, hipMemset(c->status_d.p, 0, sizeof(int)));
         OK(grow_lists(c, st));
         OK(set_rebuild_all(c));
         ++c->replays;
     }
-    if (U)
-        HIPCHK(c, hipMemcpy2DAsync(U, sizeof(double), c->U_rep_d.p, 2 * sizeof(double), sizeof(double), c->n_rep,
-                                   hipMemcpyDeviceToDevice, c->stream));
-    return read_status(c);
 }
 
 int eamfe_init_velocities(eamfe_ctx* c, double* v, int fix_com)
@@ -1631,11 +1702,14 @@ int run_range(eamfe_ctx* c, const eamfe_protocol* p, int64_t S, int64_t s0, int6
     const size_t p4 = (size_t)c->N * sizeof(double4);
     const size_t wb = (size_t)c->n_rep * sizeof(double);
     const size_t q4 = (size_t)c->N * sizeof(uint4);
+    c->last_status = -1;
     for (int64_t b = s0; b < s1; b += c->chunk) {
         const int64_t e = std::min(s1, b + c->chunk);
         if (has_eam) {
-            HIPCHK(c, hipMemcpyAsync(c->snap_P.p, cur, p4, hipMemcpyDeviceToDevice, c->stream));
-            HIPCHK(c, hipMemcpyAsync(c->snap_Q.p, Q_of(c, cur), q4, hipMemcpyDeviceToDevice, c->stream));
+            if (b > s0) {   // (the first chunk's positions are still the caller's x)
+                HIPCHK(c, hipMemcpyAsync(c->snap_P.p, cur, p4, hipMemcpyDeviceToDevice, c->stream));
+                HIPCHK(c, hipMemcpyAsync(c->snap_Q.p, Q_of(c, cur), q4, hipMemcpyDeviceToDevice, c->stream));
+            }
             HIPCHK(c, hipMemcpyAsync(c->snap_v.p, v, v3, hipMemcpyDeviceToDevice, c->stream));
             HIPCHK(c, hipMemcpyAsync(c->snap_w.p, c->W_state_d.p, wb, hipMemcpyDeviceToDevice, c->stream));
             HIPCHK(c, hipMemcpyAsync(c->snap_rows.p, c->row_acc_d.p, wb + 3 * sizeof(double), hipMemcpyDeviceToDevice,
@@ -1656,17 +1730,21 @@ int run_range(eamfe_ctx* c, const eamfe_protocol* p, int64_t S, int64_t s0, int6
             double4* start = cur;
             OK(iterate(c, a, &cur, has_eam, b, e));
             if (!has_eam) break;
-            HIPCHK(c, hipStreamSynchronize(c->stream));
             int st = 0;
-            HIPCHK(c, hipMemcpy(&st, c->status_d.p, sizeof(int), hipMemcpyDeviceToHost));
+            OK(fetch_status(c, &st));
+            c->last_status = st;
             if (!(st & (ST_NEIGH_OVERFLOW | ST_CELL_OVERFLOW))) break;
-            if (attempt >= 6) return read_status(c);
+            if (attempt >= 6) return report_status(c, st);
             HIPCHK(c, hipMemset(c->status_d.p, 0, sizeof(int)));
             drop_graphs(c);
             // back to the chunk's start, then larger rows or bins
             cur = start;
-            HIPCHK(c, hipMemcpyAsync(cur, c->snap_P.p, p4, hipMemcpyDeviceToDevice, c->stream));
-            HIPCHK(c, hipMemcpyAsync(Q_of(c, cur), c->snap_Q.p, q4, hipMemcpyDeviceToDevice, c->stream));
+            if (b > s0) {
+                HIPCHK(c, hipMemcpyAsync(cur, c->snap_P.p, p4, hipMemcpyDeviceToDevice, c->stream));
+                HIPCHK(c, hipMemcpyAsync(Q_of(c, cur), c->snap_Q.p, q4, hipMemcpyDeviceToDevice, c->stream));
+            } else {
+                OK(pack(c, x));   // into the buffers it went to before
+            }
             HIPCHK(c, hipMemcpyAsync(v, c->snap_v.p, v3, hipMemcpyDeviceToDevice, c->stream));
             HIPCHK(c, hipMemcpyAsync(c->W_state_d.p, c->snap_w.p, wb, hipMemcpyDeviceToDevice, c->stream));
             HIPCHK(c, hipMemcpyAsync(c->row_acc_d.p, c->snap_rows.p, wb + 3 * sizeof(double), hipMemcpyDeviceToDevice,
@@ -1716,8 +1794,10 @@ int run_switching(eamfe_ctx* c, const eamfe_protocol* p, int64_t s0, int64_t s1,
         HIPCHK(c, hipMemcpyAsync(lam_out, c->lam_d.p, (S + 1) * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
     if (s0 == 0) HIPCHK(c, hipMemsetAsync(c->W_state_d.p, 0, (size_t)c->n_rep * sizeof(double), c->stream));
     OK(run_range(c, p, S, s0, s1, x, v, dHdl_out, W_out, S, 0, c1, has_eam));
-    if (sync) return read_status(c);
-    return EAMFE_OK;
+    if (!sync) return EAMFE_OK;
+    if (c->last_status < 0) return read_status(c);
+    HIPCHK(c, hipStreamSynchronize(c->stream));   // nothing after the last chunk's status latches any
+    return report_status(c, c->last_status);
 }
 
 int eamfe_set_chunk(eamfe_ctx* c, int64_t steps)
@@ -2104,6 +2184,8 @@ int eamfe_pressure(eamfe_ctx* c, const double* x, const double* v, double* P)
     (void)hipSetDevice(c->device);
     OK(pack(c, x));
     OK(ensure_lists(c, c->have_list ? c->skin : 0.3, PA(c)));
+    std::vector<double> part((size_t)c->n_tiles * 3);
+    int st = 0;
     for (int attempt = 0;; ++attempt) {
         NeighArgs na = neigh_args(c, PA(c));
         LCHK(c, launch_neigh_rebuild(na, step_args(c), c->lanes, c->block, c->stream));
@@ -2120,17 +2202,15 @@ int eamfe_pressure(eamfe_ctx* c, const double* x, const double* v, double* P)
         LCHK(c, launch_density(a, c->precision, c->lanes, c->block, c->stream));
         LCHK(c, launch_force(a, c->precision, c->lanes, c->block, c->stream));
         LCHK(c, launch_finish(a, c->stream));
-        HIPCHK(c, hipStreamSynchronize(c->stream));
-        int st = 0;
-        HIPCHK(c, hipMemcpy(&st, c->status_d.p, sizeof(int), hipMemcpyDeviceToHost));
+        HIPCHK(c, hipMemcpyAsync(part.data(), c->vir_d.p, part.size() * sizeof(double), hipMemcpyDeviceToHost,
+                                 c->stream));
+        OK(fetch_status(c, &st));
         if (!(st & (ST_NEIGH_OVERFLOW | ST_CELL_OVERFLOW)) || attempt >= 6) break;
         HIPCHK(c, hipMemset(c->status_d.p, 0, sizeof(int)));
         OK(grow_lists(c, st));
         OK(set_rebuild_all(c));
         ++c->replays;
     }
-    std::vector<double> part((size_t)c->n_tiles * 3);
-    HIPCHK(c, hipMemcpy(part.data(), c->vir_d.p, part.size() * sizeof(double), hipMemcpyDeviceToHost));
     for (int r = 0; r < c->n_rep; ++r) {   // each replica's units in order
         const RepDesc& R = c->reps[r];
         const double V = R.L[0] * R.L[1] * R.L[2];
@@ -2140,7 +2220,7 @@ int eamfe_pressure(eamfe_ctx* c, const double* x, const double* v, double* P)
             P[3 * r + k] = s / V;
         }
     }
-    return read_status(c);
+    return report_status(c, st);
 }
 
 int eamfe_barostat_step(eamfe_ctx* c, const eamfe_barostat* b, int64_t step, double w_eam, double* x, double* v,

@@ -73,7 +73,6 @@ struct NeighArgs {
     const Tile* tiles;
     const RepDesc* reps;
     const int32_t* rep_of;      // [N] replica of each atom
-    const int32_t* cell_rep;    // [n_cells] replica of each cell
     const double4* P;           // [N] packed positions (x, y, z, .)
     const uint4* Q;             // [N] box coordinates frac(x/L) 2^32
     double* xref;               // SoA [3][N]
