@@ -1818,6 +1818,15 @@ __global__ __launch_bounds__(kMaxBlock) void k_force(StepArgs a)
     const double lam_it = a.step_kernel ? a.lam[it] : 0.0;
     const double lam_next = a.step_kernel && it < a.it_last ? a.lam[it + 1] : 0.0;
     uint4* const st = (uint4*)(lds_tab + 2 * nr);   // staged form: the block's replica records, after the table
+    // FP32 persistent form: a wavefront's units run through few replicas, whose
+    // noise totals it keeps (a replica of 55,296 atoms has 864 partials, as many
+    // bytes per unit as the unit's own rows: force pass 262 -> 249 us on 1.3
+    // million atoms).  Staged wavefronts have one unit or two, and summing once
+    // per block ahead of the walk was 1-2 % slower per step; FP64 has no
+    // registers left.
+    constexpr bool kKeepZ = kQ && !kStage;
+    double z_kept[3] = {0.0, 0.0, 0.0};
+    int z_rep = -1;
     auto unit = [&](const Tile& tl) {
     const RepDesc& R = a.reps[tl.rep];
     const int lane = wave_lane() % T;
@@ -1877,7 +1886,8 @@ __global__ __launch_bounds__(kMaxBlock) void k_force(StepArgs a)
     const double xiraw[3] = {xisrc[i], xisrc[N + i], xisrc[2 * N + i]};
     const double xrraw[3] = {xrsrc[i], xrsrc[N + i], xrsrc[2 * N + i]};
     PartPair<3> zp;
-    if (noise_total) zp = replica_loads<3>(a.noise_part, tbase, ntile);
+    const bool fresh = noise_total && (!kKeepZ || tl.rep != z_rep);   // uniform
+    if (fresh) zp = replica_loads<3>(a.noise_part, tbase, ntile);
     const double ks = ks_raw, eemb = eemb_raw;
     double vi[3] = {0.0, 0.0, 0.0}, xii[3] = {0.0, 0.0, 0.0}, xr[3] = {0.0, 0.0, 0.0};
 #pragma unroll
@@ -1889,7 +1899,15 @@ __global__ __launch_bounds__(kMaxBlock) void k_force(StepArgs a)
 
     // the replica's thermostat noise of this step, from the density pass's unit partials
     double zsum[3] = {0.0, 0.0, 0.0};
-    if (noise_total) replica_finish<3>(zp, a.noise_part, tbase, ntile, zsum);
+    if (fresh) replica_finish<3>(zp, a.noise_part, tbase, ntile, zsum);
+    if constexpr (kKeepZ) {
+        if (fresh) z_rep = tl.rep;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            z_kept[c] = fresh ? zsum[c] : z_kept[c];
+            zsum[c] = noise_total ? z_kept[c] : 0.0;
+        }
+    }
 
     double e[3] = {0.0, 0.0, 0.0};   // U_EAM contribution, |x - x0|^2, row length (list work of the pass)
     if (valid && lane == 0) {
