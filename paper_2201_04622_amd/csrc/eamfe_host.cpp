@@ -778,13 +778,13 @@ int plan_lists(eamfe_ctx* c, double skin, int max_neighbors)
             lds_atoms = std::max(lds_atoms, R.n);
             lds_cells = std::max(lds_cells, R.nc[0] * R.nc[1] * R.nc[2]);
         }
-    if (lds_atoms)
-        for (int wv : {16, 8, 4})
+    if (lds_atoms && rows_lds_fit(lds_atoms, lds_cells, cap, (size_t)c->max_lds))
+        for (int wv : {16, 8, 4, 2})   // two: rows of more than 3400 slots only
             if (rows_lds_bytes(lds_atoms, lds_cells, cap, wv) + 1024 <= (size_t)c->max_lds) {   // + static shared words
                 lds_waves = wv;
                 break;
             }
-    if (lds_atoms && !lds_waves) {   // not even four wavefronts fit: every replica through k_bin / k_list
+    if (lds_atoms && !lds_waves) {   // rows too wide: every replica through k_bin / k_list
         classify(false);
         lds_atoms = lds_cells = 0;
     }

@@ -189,7 +189,8 @@ constexpr int kListLds = 64 * 1024;
 // cell; at most one per cell plus two per wavefront) and per wavefront a row
 // buffer of `cap` slots and a chunk of the candidate stream (16-bit
 // positions).  The wavefronts' part also holds 16-bit ids of all atoms while
-// they are sorted (4 or more wavefronts of 2 KB and more).
+// they are sorted (8 KB: four wavefronts' chunks, or the rows
+// of two, which are taken only for rows too wide for four).
 constexpr int kRowsAtomsMax = 4096;    // replicas of at most this many atoms (16-bit ids, 64 KB of records)
 constexpr int kRowsCellsMax = 4096;    // and at most this many cells use it (12 bits of a work entry)
 constexpr int kRowsStream = 1024;      // candidates per chunk
@@ -213,6 +214,15 @@ __host__ __device__ inline size_t rows_lds_bytes(int atoms, int cells, int cap, 
 {
     const RowsWs r = rows_ws(cells, cap);
     return (size_t)atoms * 16 + r.waves + (size_t)waves * r.wave;
+}
+
+// The widest rows the builder takes: records, ids and cell starts with four row
+// buffers fit a block (with the work entries and chunks, two wavefronts then
+// fit at least).
+inline bool rows_lds_fit(int atoms, int cells, int cap, size_t max_lds)
+{
+    const auto up = [](size_t b) { return (b + 15) & ~(size_t)15; };
+    return (size_t)atoms * 16 + up((size_t)atoms * 2) + up((size_t)(cells + 1) * 4) + (size_t)cap * 16 + 1024 <= max_lds;
 }
 
 // Launchers (eamfe_kernels.hip).  Each returns a hipError_t as int.

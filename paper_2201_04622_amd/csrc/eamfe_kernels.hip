@@ -2143,7 +2143,10 @@ int launch_neigh_rebuild(const NeighArgs& a, const StepArgs& st, int lanes, int 
     }
     if (a.n_lds > 0) {
         const size_t lds = rows_lds_bytes(a.lds_atoms, a.lds_cells, a.cap, a.lds_waves);
-        const auto k = a.lds_waves >= 16 ? k_rows_lds<4> : a.lds_waves >= 8 ? k_rows_lds<8> : k_rows_lds<16>;
+        const auto k = a.lds_waves >= 16  ? k_rows_lds<4>
+                       : a.lds_waves >= 8 ? k_rows_lds<8>
+                       : a.lds_waves >= 4 ? k_rows_lds<16>
+                                          : k_rows_lds<32>;
         allow_lds(reinterpret_cast<const void*>(k), lds);
         hipLaunchKernelGGL(k, dim3(a.lds_grid), dim3(64 * a.lds_waves), lds, s, a, st);
     }
