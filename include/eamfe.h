@@ -478,11 +478,11 @@ int eamfe_adjoint_theta(eamfe_ctx* ctx, const double* x_dev, const double* w_hos
 /* eamfe_adjoint_theta for callers that cannot allocate device memory (code
  * under HIP graph capture, tight serving loops, harnesses that forbid it):
  * the same arguments, kernels and results, with the adjoint's per-call
- * scratch (its fixed-point coefficient bins and the knot transform's work
- * rows) in a fixed per-device region inside the library instead of the
- * context's workspace, so the call allocates nothing, also in a context
- * without a caller workspace (where the lists must then already fit: else
- * EAMFE_ENOMEM, nothing allocated).  The region holds 32 MiB:
+ * scratch (its fixed-point coefficient bins) in a fixed per-device region
+ * inside the library instead of the context's workspace, so the call
+ * allocates nothing, also in a context without a caller workspace (where the
+ * lists must then already fit: else EAMFE_ENOMEM, nothing allocated).  The
+ * region holds 32 MiB, and as a limit
  *   n_rep * 3 * (n_r - 1) * 32 bytes (rounded up to 256)
  *   + (reduce ? 1 : n_rep) * 3 * 2 * n_r * 8 bytes
  * must fit (116 replicas at 2000 knots with reduce = 0, 174 with

@@ -7,8 +7,10 @@
 //                prefix of the replicas whose lists are due, in blocks 0
 //                and 1; binning of those replicas' atoms into cells in the
 //                others;
-//   k_list     : Verlet rows within r_cut + skin, one wavefront per atom,
-//                each cell's members taken in id order;
+//   k_list     : Verlet rows within r_cut + skin, one wavefront per cell of a
+//                due replica, each stencil cell's members taken in id order
+//                (k_rows_lds does the work of both for replicas that fit one
+//                block's LDS);
 //   k_density  : rho_i = sum_j rho(r_ij) over the row, F(rho_i), F'(rho_i),
 //                the thermostat noise of the step with its replica sum, and
 //                the bin counters of the rebuilt replicas cleared;
