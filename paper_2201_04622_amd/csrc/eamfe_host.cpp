@@ -1687,17 +1687,26 @@ namespace {
 // crystal collapses into dense clusters) restores the chunk's starting
 // state, enlarges the capacity and replays the chunk; the noise is a
 // function of (seed, atom, step), so the replay is the trajectory the run
-// would have had.
+// would have had.  Planning or enlarging the lists can move an arena that the
+// library owns: every address into it is looked up again after either (which
+// of the two position buffers is current, and the tuner's copies as x and v).
 int run_range(eamfe_ctx* c, const eamfe_protocol* p, int64_t S, int64_t s0, int64_t s1, double* x, double* v,
               double* dHdl_out, double* W_out, int64_t stride, int64_t trace_off, double c1, bool has_eam)
 {
     if (has_eam && c->adj_every > 0) OK(check_adjoint_tables(c, "adjoint sampling"));   // before any step runs
     drop_graphs(c);   // captured kernel arguments belong to one call (pointers, protocol, shapes)
     OK(pack(c, x));
-    double4* cur = PA(c);
+    const bool tuner = x == (double*)c->tune_x.p;   // x and v are the tuner's copies
+    const auto moved = [&] {
+        if (!tuner) return;
+        x = (double*)c->tune_x.p;
+        v = (double*)c->tune_v.p;
+    };
     c->resume_step = s0;   // nothing has run if the lists do not fit
-    if (has_eam) OK(ensure_lists(c, p->skin, cur));
+    if (has_eam) OK(ensure_lists(c, p->skin, PA(c)));
     c->resume_step = -1;
+    moved();
+    double4* cur = PA(c);
     const size_t v3 = 3 * (size_t)c->N * sizeof(double);
     const size_t p4 = (size_t)c->N * sizeof(double4);
     const size_t wb = (size_t)c->n_rep * sizeof(double);
@@ -1727,7 +1736,7 @@ int run_range(eamfe_ctx* c, const eamfe_protocol* p, int64_t S, int64_t s0, int6
             a.fix_com = p->fix_com ? 1 : 0;
             a.dt = p->dt;
             a.c1 = c1;
-            double4* start = cur;
+            const bool start_b = cur == PB(c);
             OK(iterate(c, a, &cur, has_eam, b, e));
             if (!has_eam) break;
             int st = 0;
@@ -1738,7 +1747,7 @@ int run_range(eamfe_ctx* c, const eamfe_protocol* p, int64_t S, int64_t s0, int6
             HIPCHK(c, hipMemset(c->status_d.p, 0, sizeof(int)));
             drop_graphs(c);
             // back to the chunk's start, then larger rows or bins
-            cur = start;
+            cur = start_b ? PB(c) : PA(c);
             if (b > s0) {
                 HIPCHK(c, hipMemcpyAsync(cur, c->snap_P.p, p4, hipMemcpyDeviceToDevice, c->stream));
                 HIPCHK(c, hipMemcpyAsync(Q_of(c, cur), c->snap_Q.p, q4, hipMemcpyDeviceToDevice, c->stream));
@@ -1764,6 +1773,8 @@ int run_range(eamfe_ctx* c, const eamfe_protocol* p, int64_t S, int64_t s0, int6
                 return g;
             }
             OK(g);
+            moved();
+            cur = start_b ? PB(c) : PA(c);
             OK(set_rebuild_all(c));
         }
     }
