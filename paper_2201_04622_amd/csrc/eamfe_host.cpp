@@ -820,14 +820,31 @@ int plan_lists(eamfe_ctx* c, double skin, int max_neighbors)
     return EAMFE_OK;
 }
 
+__global__ void k_fill_i32(int32_t* p, int n, int32_t v)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) p[i] = v;
+}
+
+int set_rebuild_all(eamfe_ctx* c)
+{
+    hipLaunchKernelGGL(k_fill_i32, dim3((c->n_rep + 255) / 256), dim3(256), 0, c->stream, (int32_t*)c->rebuild_d.p,
+                       c->n_rep, 1);
+    HIPCHK(c, hipGetLastError());
+    return EAMFE_OK;
+}
+
 // Row or bin overflow seen (status bits st): ask for larger rows or bins and
-// plan the lists again (EAMFE_ENOMEM if they do not fit the workspace).
+// plan the lists again (EAMFE_ENOMEM if they do not fit the workspace: the rows
+// on the device stay truncated and are due again in the next pass).
 int grow_lists(eamfe_ctx* c, int st)
 {
     const int new_cap = (st & ST_NEIGH_OVERFLOW) ? (int)(std::ceil(c->cap * 1.5 / 32.0) * 32.0) : c->cap;
     if (st & ST_CELL_OVERFLOW) c->min_ccap = (int)(std::ceil(c->ccap * 1.5 / 32.0) * 32.0);
     c->cap_min = std::max<long>(c->cap_min, new_cap);
-    return plan_lists(c, c->skin, new_cap);
+    const int rc = plan_lists(c, c->skin, new_cap);
+    if (rc) OK(set_rebuild_all(c));
+    return rc;
 }
 
 int status_code(int st)
@@ -852,10 +869,13 @@ int fetch_status(eamfe_ctx* c, int* st)
     return EAMFE_OK;
 }
 
-// The status st (just fetched) as the call's result; latched conditions are cleared.
+// The status st (just fetched) as the call's result; latched conditions are
+// cleared.  Rows that overflowed are truncated: they are due again in the next
+// pass, which then meets the overflow itself.
 int report_status(eamfe_ctx* c, int st)
 {
     if (st) {
+        if (st & (ST_NEIGH_OVERFLOW | ST_CELL_OVERFLOW)) OK(set_rebuild_all(c));
         HIPCHK(c, hipMemset(c->status_d.p, 0, sizeof(int)));
         const int code = status_code(st);
         const char* what = code == EAMFE_ENEIGH_OVERFLOW ? "neighbour row overflow (raise max_neighbors)"
@@ -879,20 +899,6 @@ __global__ void k_set_i64(int64_t* p, int64_t v) { *p = v; }
 int set_iter(eamfe_ctx* c, int64_t v)
 {
     hipLaunchKernelGGL(k_set_i64, dim3(1), dim3(1), 0, c->stream, (int64_t*)c->iter_d.p, v);
-    HIPCHK(c, hipGetLastError());
-    return EAMFE_OK;
-}
-
-__global__ void k_fill_i32(int32_t* p, int n, int32_t v)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
-}
-
-int set_rebuild_all(eamfe_ctx* c)
-{
-    hipLaunchKernelGGL(k_fill_i32, dim3((c->n_rep + 255) / 256), dim3(256), 0, c->stream, (int32_t*)c->rebuild_d.p,
-                       c->n_rep, 1);
     HIPCHK(c, hipGetLastError());
     return EAMFE_OK;
 }

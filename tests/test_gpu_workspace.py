@@ -104,3 +104,62 @@ def test_fp32_accumulation_forms_match_the_oracle(opot, deterministic):
     say(f"deterministic={deterministic}: forces bitwise equal across lanes 1 and 4: {same}")
     if deterministic:
         assert same                        # fixed point: independent of the launch shape
+
+
+@pytest.mark.parametrize("call", ["forces", "pressure"])
+@pytest.mark.parametrize("prec", [FP64, FP32])
+def test_overflow_beyond_the_workspace_in_one_evaluation(prec, call):
+    # rows of 64 slots hold the crystal's 54 neighbours, not all of the displaced atoms' (up to 68), and the
+    # larger rows do not fit the workspace: the call comes back for a larger one and is repeated, and must
+    # then build whole rows, not go on with the truncated ones
+    import torch
+
+    import paper_2201_04622_amd.eamfe as E
+    reps = [I.Replica("fcc", 5, I.A_FCC_VERBATIM, 300.0, 5.0, 1), I.Replica("fcc", 11, I.A_FCC_VERBATIM, 300.0, 5.0, 2)]
+    out = []
+    for cap in (64, 0):
+        ctx, x0, arrs = make_ctx(reps, prec)
+        x = E.to_soa(I.displaced(arrs["x0"], 0.2, seed=5))
+        ctx.neigh_build(x0, 0.3, cap)
+        held = ctx.workspace_bytes()[1]
+        if call == "forces":
+            f, U = torch.zeros_like(x), torch.zeros(2, dtype=torch.float64, device="cuda")
+            ctx.eam_forces(x, f, U)
+            out.append(np.concatenate([f.cpu().numpy().ravel(), U.cpu().numpy()]))
+        else:
+            out.append(ctx.pressure(x).ravel())
+        assert (ctx.workspace_bytes()[1] > held) == (cap == 64)
+        say(f"{call} prec {prec} cap {cap}: rows {ctx.list_stats()}")
+        assert ctx.list_stats()[1] > 64
+        ctx.close()
+    assert np.array_equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("prec", [FP64, FP32])
+def test_no_call_goes_on_with_rows_that_overflowed(prec):
+    # a force call after a refused row capacity builds whole rows; a knot gradient, which reports an overflow and
+    # does not retry, reports it again
+    import torch
+
+    import paper_2201_04622_amd.eamfe as E
+    reps = [I.Replica("fcc", 5, I.A_FCC_VERBATIM, 300.0, 5.0, 1), I.Replica("fcc", 11, I.A_FCC_VERBATIM, 300.0, 5.0, 2)]
+    out = []
+    for cap in (32, 0):
+        ctx, x0, arrs = make_ctx(reps, prec)
+        x = E.to_soa(I.displaced(arrs["x0"], 0.2, seed=5))
+        f = torch.zeros_like(x)
+        d = torch.zeros(2, 3, I.N_KNOTS, dtype=torch.float64, device="cuda")
+        if cap:
+            for call in (lambda: ctx.neigh_build(x, 0.3, cap), lambda: ctx.adjoint_theta(x, d),
+                         lambda: ctx.adjoint_theta(x, d)):
+                with pytest.raises(E.EamfeError) as e:
+                    call()
+                assert e.value.code == 6
+            d.zero_()
+        ctx.eam_forces(x, f)
+        ctx.adjoint_theta(x, d)
+        assert ctx.list_stats()[1] > 64
+        out.append((f.cpu().numpy(), d.cpu().numpy()))
+        ctx.close()
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
