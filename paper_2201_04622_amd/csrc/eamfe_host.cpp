@@ -343,7 +343,8 @@ int bind(eamfe_ctx* c, const Shape& s)
         if (e != hipSuccess) return fail(c, EAMFE_ENOMEM, std::string("hipMalloc: ") + hipGetErrorString(e));
         if (c->arena) {
             const size_t used = layout_bytes(c, c->shape);
-            HIPCHK(c, hipMemcpy(p, c->arena, used, hipMemcpyDeviceToDevice));
+            HIPCHK(c, hipMemcpyAsync(p, c->arena, used, hipMemcpyDeviceToDevice, c->stream));
+            HIPCHK(c, hipStreamSynchronize(c->stream));
             (void)hipFree(c->arena);
         }
         c->arena = (char*)p;
@@ -373,7 +374,10 @@ int bind(eamfe_ctx* c, const Shape& s)
     c->shape = s;
     c->need = 0;
     drop_graphs(c);   // captured launches hold buffer addresses
-    if (new_len[G_CORE] && !old_len[G_CORE]) HIPCHK(c, hipMemset(c->status_d.p, 0, new_len[G_CORE]));
+    if (new_len[G_CORE] && !old_len[G_CORE]) {
+        HIPCHK(c, hipMemsetAsync(c->status_d.p, 0, new_len[G_CORE], c->stream));
+        HIPCHK(c, hipStreamSynchronize(c->stream));   // (the next call may be on another stream)
+    }
     const bool tab_moved = old_off[G_TAB] != new_off[G_TAB] || old_len[G_TAB] != new_len[G_TAB];
     const bool lam_moved = old_off[G_LAM] != new_off[G_LAM] || old_len[G_LAM] != new_len[G_LAM];
     if (tab_moved && c->have_pot && s.n_r == old.n_r && s.n_rho == old.n_rho) OK(upload_tables(c));
@@ -869,6 +873,15 @@ int fetch_status(eamfe_ctx* c, int* st)
     return EAMFE_OK;
 }
 
+// Clears the latched status, in order with the context's stream (which may be
+// one that the null stream does not wait for): ahead of a retried pass, whose
+// conditions it must not wipe out.
+int clear_status(eamfe_ctx* c)
+{
+    HIPCHK(c, hipMemsetAsync(c->status_d.p, 0, sizeof(int), c->stream));
+    return EAMFE_OK;
+}
+
 // The status st (just fetched) as the call's result; latched conditions are
 // cleared.  Rows that overflowed are truncated: they are due again in the next
 // pass, which then meets the overflow itself.
@@ -876,7 +889,8 @@ int report_status(eamfe_ctx* c, int st)
 {
     if (st) {
         if (st & (ST_NEIGH_OVERFLOW | ST_CELL_OVERFLOW)) OK(set_rebuild_all(c));
-        HIPCHK(c, hipMemset(c->status_d.p, 0, sizeof(int)));
+        OK(clear_status(c));
+        HIPCHK(c, hipStreamSynchronize(c->stream));   // (the next call may be on another stream)
         const int code = status_code(st);
         const char* what = code == EAMFE_ENEIGH_OVERFLOW ? "neighbour row overflow (raise max_neighbors)"
                            : code == EAMFE_ECELL_OVERFLOW ? "cell bin overflow"
@@ -1342,8 +1356,10 @@ int eamfe_set_workspace(eamfe_ctx* c, void* dev, size_t bytes)
     (void)hipSetDevice(c->device);
     HIPCHK(c, hipStreamSynchronize(c->stream));
     // every live buffer keeps its offset: one copy moves them all
-    if (c->arena && used && (char*)dev != c->arena)
-        HIPCHK(c, hipMemcpy(dev, c->arena, used, hipMemcpyDeviceToDevice));
+    if (c->arena && used && (char*)dev != c->arena) {
+        HIPCHK(c, hipMemcpyAsync(dev, c->arena, used, hipMemcpyDeviceToDevice, c->stream));
+        HIPCHK(c, hipStreamSynchronize(c->stream));   // (the old workspace may be reused at once)
+    }
     if (c->arena && !c->caller_ws) (void)hipFree(c->arena);
     c->arena = (char*)dev;
     c->arena_bytes = bytes;
@@ -1609,7 +1625,7 @@ int neigh_build(eamfe_ctx* c, const double* x, double skin, int max_neighbors)
         int st = 0;
         OK(fetch_status(c, &st));
         if (!(st & (ST_NEIGH_OVERFLOW | ST_CELL_OVERFLOW))) return report_status(c, st);
-        HIPCHK(c, hipMemset(c->status_d.p, 0, sizeof(int)));
+        OK(clear_status(c));
         OK(grow_lists(c, st));
     }
     return read_status(c);
@@ -1646,7 +1662,7 @@ int eam_forces(eamfe_ctx* c, const double* x, double* f, double* U, double* e_at
         OK(fetch_status(c, &st));
         if (!(st & (ST_NEIGH_OVERFLOW | ST_CELL_OVERFLOW)) || attempt >= 6) return report_status(c, st);
         // rows or bins too small for this configuration: enlarge and evaluate again
-        HIPCHK(c, hipMemset(c->status_d.p, 0, sizeof(int)));
+        OK(clear_status(c));
         OK(grow_lists(c, st));
         OK(set_rebuild_all(c));
         ++c->replays;
@@ -1750,7 +1766,7 @@ int run_range(eamfe_ctx* c, const eamfe_protocol* p, int64_t S, int64_t s0, int6
             c->last_status = st;
             if (!(st & (ST_NEIGH_OVERFLOW | ST_CELL_OVERFLOW))) break;
             if (attempt >= 6) return report_status(c, st);
-            HIPCHK(c, hipMemset(c->status_d.p, 0, sizeof(int)));
+            OK(clear_status(c));
             drop_graphs(c);
             // back to the chunk's start, then larger rows or bins
             cur = start_b ? PB(c) : PA(c);
@@ -1868,7 +1884,9 @@ int eamfe_get_state(eamfe_ctx* c, double* W, double* xref, double* skin)
     if (W) HIPCHK(c, hipMemcpy(W, c->W_state_d.p, (size_t)c->n_rep * sizeof(double), hipMemcpyDeviceToHost));
     if (xref) {
         if (!c->have_list) return fail(c, EAMFE_ESTATE, "get_state: no neighbour lists have been built");
-        HIPCHK(c, hipMemcpy(xref, c->xref_d.p, (size_t)3 * c->N * sizeof(double), hipMemcpyDeviceToDevice));
+        HIPCHK(c, hipMemcpyAsync(xref, c->xref_d.p, (size_t)3 * c->N * sizeof(double), hipMemcpyDeviceToDevice,
+                                 c->stream));
+        HIPCHK(c, hipStreamSynchronize(c->stream));
     }
     if (skin) *skin = c->have_list ? c->skin : 0.0;
     return EAMFE_OK;
@@ -2223,7 +2241,7 @@ int eamfe_pressure(eamfe_ctx* c, const double* x, const double* v, double* P)
                                  c->stream));
         OK(fetch_status(c, &st));
         if (!(st & (ST_NEIGH_OVERFLOW | ST_CELL_OVERFLOW)) || attempt >= 6) break;
-        HIPCHK(c, hipMemset(c->status_d.p, 0, sizeof(int)));
+        OK(clear_status(c));
         OK(grow_lists(c, st));
         OK(set_rebuild_all(c));
         ++c->replays;
