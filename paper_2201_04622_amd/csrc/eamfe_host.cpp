@@ -131,7 +131,7 @@ struct eamfe_ctx {
     int lds_rows = 1;                       // 0: every replica through k_bin / k_list
     int n_lds = 0, n_global = 0, lds_atoms = 0, lds_cells = 0, lds_waves = 0;
     DevBuf lds_list_d;                      // [n_rep] those replicas, in order
-    std::vector<int32_t> lds_list_h;        // as uploaded
+    std::vector<int32_t> lds_list_h;        // as it stands on the device (empty: not known)
 
     // graph replay of the middle iterations (0 = eager launches)
     int graph_iters = 0;
@@ -329,7 +329,7 @@ int bind(eamfe_ctx* c, const Shape& s)
         return EAMFE_OK;
     }
     HIPCHK(c, hipStreamSynchronize(c->stream));   // no pass in flight uses the old layout
-    c->lds_list_h.clear();                        // (the list group may move: uploaded again)
+    c->lds_list_h.clear();                        // (it moves with the system group: uploaded again)
     if (need > c->arena_bytes) {
         if (c->caller_ws || c->no_alloc) {
             c->need = need;
@@ -808,7 +808,7 @@ int plan_lists(eamfe_ctx* c, double skin, int max_neighbors)
     c->lds_waves = lds_waves;
     drop_graphs(c);   // captured launches hold the old skin and builders
     if (lds_list != c->lds_list_h) {   // (the copy is waited for with the replicas' below)
-        c->lds_list_h = lds_list;
+        c->lds_list_h.clear();
         if (!lds_list.empty())
             HIPCHK(c, hipMemcpyAsync(c->lds_list_d.p, lds_list.data(), lds_list.size() * sizeof(int32_t),
                                      hipMemcpyHostToDevice, c->stream));
@@ -821,6 +821,7 @@ int plan_lists(eamfe_ctx* c, double skin, int max_neighbors)
     HIPCHK(c, hipMemsetAsync(c->cell_cnt_d.p, 0, (size_t)std::max(1, n_cells) * sizeof(int32_t), c->stream));
     HIPCHK(c, hipMemsetAsync(c->nnb_d.p, 0, (size_t)c->N * sizeof(int32_t), c->stream));
     OK(upload_reps(c));
+    c->lds_list_h = lds_list;   // known to be there
     return EAMFE_OK;
 }
 
