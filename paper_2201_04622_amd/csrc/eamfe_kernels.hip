@@ -777,16 +777,31 @@ __global__ __launch_bounds__(kBinBlock) void k_bin(NeighArgs a, StepArgs s)
 // beyond), so the cells need no sorting pass of their own.  A stream that fits
 // one chunk (the usual case) then goes into registers once, up to 16 records
 // per lane, and every atom of the cell is tested against them with exact
-// minimum-image box coordinates; a longer one is staged anew for every atom.
-// Accepted candidates go in stream order (ballot and prefix count) to a row
-// buffer in LDS, written out as whole 16-byte slabs.  Bound by the tests'
-// arithmetic; with a wavefront per atom every atom staged and gathered its
-// 125 cells anew.  All 128,000 atoms of eight replicas, rows of 179: 399 -> 134
-// us; 1.3 million atoms, rows of 77 (2.4 atoms per cell): 2327 -> 1424 us.
+// minimum-image box coordinates.  Accepted candidates go in stream order
+// (ballot and prefix count) to a row buffer in LDS, written out as whole
+// 16-byte slabs.  A longer stream goes through the registers in pieces, and
+// the atoms' rows grow by each piece's share.  Where there are fewer cells
+// than half the wavefronts (as many as are resident), a cell's atoms are dealt
+// out to several.  Bound by the tests' arithmetic; with a wavefront per atom
+// every atom staged and gathered its 125 cells anew.  All 128,000 atoms of
+// eight replicas, rows of 179: 399 -> 138 us; 1.3 million atoms, rows of 77
+// (2.4 atoms per cell): 2569 -> 1440.  Streams of 1054: eight replicas of 18,522
+// atoms, rows of 253, 640 -> 230 (597 when each atom staged the stream anew),
+// one of 4,394 atoms 33 -> 37 (112 with each cell's atoms in one wavefront).
 constexpr int kListBlock = 256;
 constexpr int kListGrid = 2048;
 constexpr int kStencil = 125;   // 5 x 5 x 5 cells
 constexpr int kListCand = 16;   // candidates per lane held in registers
+constexpr int kListLong = 12;   // of a longer stream at a time (sixteen spill)
+constexpr int kListParts = 16;  // wavefronts per item, at most
+
+// Candidates in registers, K per lane: box coordinates and local ids (-1: none).
+template <int K>
+struct ListChunk {
+    static constexpr int held = 64 * K;
+    uint32_t x[K], y[K], z[K];
+    int id[K];
+};
 
 __global__ __launch_bounds__(kListBlock, 4) void k_list(NeighArgs a, int n_rep)
 {
@@ -800,17 +815,13 @@ __global__ __launch_bounds__(kListBlock, 4) void k_list(NeighArgs a, int n_rep)
     int* cb = rowbuf + (size_t)(kListBlock / 64) * cap + (size_t)w * a.chunk;   // this wave's candidate chunk
     const int32_t* pre = a.flag_pre + n_rep + 1;
     const int waves = gridDim.x * (kListBlock / 64);
-    // the wave's first item: its replica's probes go out with the total's
-    // read (the empty asm takes their results before the loop's test, so the
-    // compiler cannot sink them behind it)
-    const int f0 = blockIdx.x * (kListBlock / 64) + w;
     const int total = pre[n_rep];
-    int plo0, off0;
-    const int lo0 = item_replica(pre, a.reps, n_rep, f0, plo0, off0);
-    __asm__ volatile("" : : "v"(lo0), "v"(plo0), "v"(off0));
-    for (int f = f0; f < total; f += waves) {
-        int plo = plo0, roff = off0;
-        const int lo = f == f0 ? lo0 : item_replica(pre, a.reps, n_rep, f, plo, roff);
+    if (total == 0) return;
+    const int parts = max(1, min(kListParts, waves / 2 / total));   // of an item's atoms
+    for (int fp = blockIdx.x * (kListBlock / 64) + w; fp < total * parts; fp += waves) {
+        const int f = fp / parts, part = fp - f * parts;
+        int plo, roff;
+        const int lo = item_replica(pre, a.reps, n_rep, f, plo, roff);
         const RepDesc& R = a.reps[lo];
         const int il0 = f - plo;   // the item within its replica: a cell, or a group of atoms
         const int rn = R.n, nc0 = R.nc[0], nc1 = R.nc[1], nc2 = R.nc[2], cbase = R.cell_base;
@@ -847,31 +858,32 @@ __global__ __launch_bounds__(kListBlock, 4) void k_list(NeighArgs a, int n_rep)
             __builtin_amdgcn_wave_barrier();   // the row buffer is reused by the next atom
             cnt = 0;
         };
-        // the candidates of registers k = 0 .. kListCand - 1, from local ids
-        uint32_t cx_[kListCand], cy_[kListCand], cz_[kListCand];
-        int cj[kListCand];
-        auto load = [&](int n, auto&& id_at) {
+        // n candidates (as many as the chunk holds) from local ids into registers
+        auto load = [&](auto& ch, int n, auto&& id_at) {
+            constexpr int K = std::decay_t<decltype(ch)>::held / 64;
 #pragma unroll
-            for (int k = 0; k < kListCand; ++k) {
-                cx_[k] = cy_[k] = cz_[k] = 0u;
-                cj[k] = -1;
+            for (int k = 0; k < K; ++k) {
+                ch.x[k] = ch.y[k] = ch.z[k] = 0u;
+                ch.id[k] = -1;
                 if (64 * k < n) {   // uniform
-                    cj[k] = lw < n - 64 * k ? id_at(64 * k) : -1;
-                    const uint4 q = a.Q[roff + max(cj[k], 0)];
-                    cx_[k] = q.x;
-                    cy_[k] = q.y;
-                    cz_[k] = q.z;
+                    ch.id[k] = lw < n - 64 * k ? id_at(64 * k) : -1;
+                    const uint4 q = a.Q[roff + max(ch.id[k], 0)];
+                    ch.x[k] = q.x;
+                    ch.y[k] = q.y;
+                    ch.z[k] = q.z;
                 }
             }
         };
-        auto test_regs = [&](const uint4& qi, int il, int n) {
+        auto test_regs = [&](const auto& ch, const uint4& qi, int il, int n) {
+            constexpr int K = std::decay_t<decltype(ch)>::held / 64;
 #pragma unroll
-            for (int k = 0; k < kListCand; ++k)
-                if (64 * k < n) test(qi, il, cj[k], cx_[k], cy_[k], cz_[k]);
+            for (int k = 0; k < K; ++k)
+                if (64 * k < n) test(qi, il, ch.id[k], ch.x[k], ch.y[k], ch.z[k]);
         };
+        using Whole = ListChunk<kListCand>;
+        using Piece = ListChunk<kListLong>;
         // own atoms, up to 64 at a time, one per lane: record and reference position
-        auto rows_of = [&](int count, int own, auto&& one_row) {
-            const int i = roff + own;
+        auto own_record = [&](int count, int i) {
             const uint4 q = a.Q[i];
             if (lw < count) {
                 const double4 p = a.P[i];
@@ -879,27 +891,63 @@ __global__ __launch_bounds__(kListBlock, 4) void k_list(NeighArgs a, int n_rep)
                 a.xref[N + i] = p.y;
                 a.xref[2 * N + i] = p.z;
             }
+            return q;
+        };
+        auto lane_record = [&](const uint4& q, int t) {
+            return make_uint4((uint32_t)__builtin_amdgcn_readlane((int)q.x, t),
+                              (uint32_t)__builtin_amdgcn_readlane((int)q.y, t),
+                              (uint32_t)__builtin_amdgcn_readlane((int)q.z, t), 0u);
+        };
+        // their rows from the n candidates in registers
+        auto rows_of = [&](const Whole& ch, int count, int own, int n) {
+            const uint4 q = own_record(count, roff + own);
             for (int t = 0; t < count; ++t) {
                 const int il = __builtin_amdgcn_readlane(own, t);
-                const uint4 qi = make_uint4((uint32_t)__builtin_amdgcn_readlane((int)q.x, t),
-                                            (uint32_t)__builtin_amdgcn_readlane((int)q.y, t),
-                                            (uint32_t)__builtin_amdgcn_readlane((int)q.z, t), 0u);
-                one_row(qi, il);
+                test_regs(ch, lane_record(q, t), il, n);
                 write(roff + il);
             }
         };
+        // their rows from a stream longer than the registers: chunks(body) calls
+        // body(piece, n) with each n candidates in registers, and what is in range
+        // of each goes behind the row's slots so far
+        auto long_rows_of = [&](int count, int own, auto&& chunks) {
+            const int i = roff + own;
+            const uint4 q = own_record(count, i);
+            int len = 0;   // lane t: the row length of own atom t so far
+            chunks([&](const Piece& ch, int n) {
+                for (int t = 0; t < count; ++t) {
+                    const int il = __builtin_amdgcn_readlane(own, t), at = __builtin_amdgcn_readlane(len, t);
+                    test_regs(ch, lane_record(q, t), il, n);
+                    __builtin_amdgcn_wave_barrier();
+                    for (int k = lw; k < min(cnt, cap - at); k += 64) a.nbr[slot_index(roff + il, at + k, N)] = row[k];
+                    __builtin_amdgcn_wave_barrier();   // the row buffer is reused
+                    len += lw == t ? cnt : 0;
+                    cnt = 0;
+                }
+            });
+            if (lw < count) {
+                const int used = min(len, cap), pad_end = min((used + 3) & ~3, cap);
+                for (int k = used; k < pad_end; ++k) a.nbr[slot_index(i, k, N)] = i;
+                if (len > cap) atomicOr(a.status, ST_NEIGH_OVERFLOW);
+                a.nnb[i] = used;
+            }
+        };
         if (nc0 == 0) {   // all-pairs rows of a group of atoms: every other atom in id order
-            const int first = il0 * kPairAtoms, count = min(kPairAtoms, rn - first);
+            const int all = min(kPairAtoms, rn - il0 * kPairAtoms);
+            const int first = il0 * kPairAtoms + all * part / parts;
+            const int count = il0 * kPairAtoms + all * (part + 1) / parts - first;
+            if (count == 0) continue;
             const int own = min(first + lw, rn - 1);
-            if (rn <= 64 * kListCand) {
-                load(rn, [&](int k) { return k + lw; });
-                rows_of(count, own, [&](const uint4& qi, int il) { test_regs(qi, il, rn); });
+            if (rn <= Whole::held) {
+                Whole ch;
+                load(ch, rn, [&](int k) { return k + lw; });
+                rows_of(ch, count, own, rn);
             } else {
-                rows_of(count, own, [&](const uint4& qi, int il) {
-                    for (int s0 = 0; s0 < rn; s0 += 64) {
-                        const int jl = s0 + lw < rn ? s0 + lw : -1;
-                        const uint4 q = a.Q[roff + max(jl, 0)];
-                        test(qi, il, jl, q.x, q.y, q.z);
+                long_rows_of(count, own, [&](auto&& body) {
+                    for (int s0 = 0; s0 < rn; s0 += Piece::held) {
+                        Piece ch;
+                        load(ch, rn - s0, [&](int k) { return s0 + k + lw; });
+                        body(ch, rn - s0);
                     }
                 });
             }
@@ -921,8 +969,9 @@ __global__ __launch_bounds__(kListBlock, 4) void k_list(NeighArgs a, int n_rep)
             }
         }
         constexpr int kOwn = kStencil / 2;   // the cell itself
-        const int members = __builtin_amdgcn_readlane(n_c[0], kOwn);
-        if (members == 0) continue;
+        const int all = __builtin_amdgcn_readlane(n_c[0], kOwn);
+        const int m0 = all * part / parts, m1 = all * (part + 1) / parts;   // this wavefront's members
+        if (m0 == m1) continue;
         int tot_c = 0;   // running total of the stencil cells' sizes
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -937,15 +986,17 @@ __global__ __launch_bounds__(kListBlock, 4) void k_list(NeighArgs a, int n_rep)
         __builtin_amdgcn_wave_barrier();
         // stages the stream from stencil cell q0 on (`base` candidates before
         // it); returns its length, and the next cell in q1
+        const bool whole = tot_c <= min(Whole::held, a.chunk);
+        const int room = whole ? a.chunk : min(a.chunk, max(Piece::held, a.ccap));
         auto stage = [&](int q0, int base, int& q1) {
             // the cells (up to 128, two per lane) whose members fit the chunk
-            // (a cell always does: chunk >= ccap)
+            // (a cell always does: room >= ccap)
             __builtin_amdgcn_wave_barrier();
             q1 = q0;
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const int qq = q0 + 64 * h + lw;
-                const int c = __popcll(__ballot(qq < kStencil && cend[w][qq] - base <= a.chunk));
+                const int c = __popcll(__ballot(qq < kStencil && cend[w][qq] - base <= room));
                 if (q1 == q0 + 64 * h) q1 += c;   // uniform
             }
             q1 = q1 > q0 ? q1 : q0 + 1;
@@ -1028,32 +1079,26 @@ __global__ __launch_bounds__(kListBlock, 4) void k_list(NeighArgs a, int n_rep)
             return end;
         };
         int q1;
-        if (tot_c <= min(64 * kListCand, a.chunk)) {   // one chunk: the stream in registers
+        if (whole) {   // one chunk: the stream in registers
             stage(0, 0, q1);
             const int own0 = cend[w][kOwn - 1];
-            load(tot_c, [&](int k) { return cb[k + lw]; });
-            for (int g = 0; g < members; g += 64) {
-                const int count = min(64, members - g);
-                const int own = cb[own0 + g + min(lw, count - 1)];
-                rows_of(count, own, [&](const uint4& qi, int il) { test_regs(qi, il, tot_c); });
+            Whole ch;
+            load(ch, tot_c, [&](int k) { return cb[k + lw]; });
+            for (int g = m0; g < m1; g += 64) {
+                const int count = min(64, m1 - g);
+                rows_of(ch, count, cb[own0 + g + min(lw, count - 1)], tot_c);
             }
         } else {
-            for (int g = 0; g < members; g += 64) {
-                const int count = min(64, members - g);
+            for (int g = m0; g < m1; g += 64) {
+                const int count = min(64, m1 - g);
                 stage(kOwn, cend[w][kOwn - 1], q1);   // the cell's own members in id order
-                const int own = cb[g + min(lw, count - 1)];
-                rows_of(count, own, [&](const uint4& qi, int il) {
+                long_rows_of(count, cb[g + min(lw, count - 1)], [&](auto&& body) {
                     for (int q0 = 0, base = 0; q0 < kStencil;) {
                         const int end = stage(q0, base, q1);
-                        for (int k0 = 0; k0 < end; k0 += 64 * 4) {   // four reads in flight
-                            int jl[4];
-                            uint4 qj[4];
-#pragma unroll
-                            for (int u = 0; u < 4; ++u) jl[u] = k0 + 64 * u + lw < end ? cb[k0 + 64 * u + lw] : -1;
-#pragma unroll
-                            for (int u = 0; u < 4; ++u) qj[u] = a.Q[roff + max(jl[u], 0)];
-#pragma unroll
-                            for (int u = 0; u < 4; ++u) test(qi, il, jl[u], qj[u].x, qj[u].y, qj[u].z);
+                        for (int k0 = 0; k0 < end; k0 += Piece::held) {
+                            Piece ch;
+                            load(ch, end - k0, [&](int k) { return cb[k0 + k + lw]; });
+                            body(ch, end - k0);
                         }
                         base = cend[w][q1 - 1];
                         q0 = q1;
