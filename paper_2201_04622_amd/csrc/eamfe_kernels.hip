@@ -1122,13 +1122,18 @@ __global__ __launch_bounds__(kListBlock, 4) void k_list(NeighArgs a, int n_rep)
 // tests every one of its atoms against them.  In the sorted order the five
 // cells of a stencil line along z are one run of records (two where they
 // wrap), so the stream is 25 runs, whose positions 50 lanes write out to LDS,
-// and its reads are nearly consecutive.  Bound by the tests' arithmetic (about
+// and its reads are nearly consecutive.  A longer stream goes through the
+// registers in pieces, each tested against all the atoms, whose rows grow by
+// each piece's share.  Bound by the tests' arithmetic (about
 // 24 instructions per 64 candidates and atom); with a wavefront per atom that
 // read all 125 cells' members anew the LDS reads bound it.  All 113,090 atoms
-// of the 64-replica batch: 197 -> 107 us; the two 2048-atom replicas of a
-// smaller run (16 atoms per block): 27 -> 19 us.
+// of the 64-replica batch: 191 -> 107 us; at the stable lattice constants and a
+// skin of 0.45 (streams up to 1157) 506 -> 166 (467 when every atom wrote the
+// stream out again); the two 2048-atom replicas of a smaller run (16 atoms
+// per block): 26 -> 16 us.  A box of 128 atoms with all-pairs rows: 5.8 -> 7.1.
 // --------------------------------------------------------------------------
 constexpr int kCand = 16;              // candidates per lane held in registers
+constexpr int kCandLong = 12;          // of a longer stream at a time (sixteen spill)
 static_assert(64 * kCand == kRowsStream, "one chunk of the stream fills the registers");
 
 // One chunk of a candidate stream, K per lane: box coordinates, and local ids
@@ -1388,17 +1393,33 @@ __device__ __forceinline__ void build_rows(const NeighArgs& a, const RowsGeom& g
                 test(ch, qi, 0);
                 write(roff + (int)qi.w);
             }
-        } else {
-            for (int mb = m0; mb < m1; ++mb) {
-                const uint4 qi = st[mb];
-                if ((int)qi.w >= a1) break;
-                cnt = 0;
-                for (int base = 0; base < total; base += 64 * 4) {   // small chunks: few registers
-                    RowsChunk<4> ch;
+        } else {   // chunk by chunk, each member's row growing by what is in range of the chunk
+            for (int g = m0; g < m1; g += 64) {
+                const int ge = min(g + 64, m1);
+                int len = 0;   // lane t: the row length of member g + t so far
+                for (int base = 0; base < total; base += 64 * kCandLong) {
+                    RowsChunk<kCandLong> ch;
                     load(ch, base);
-                    test(ch, qi, base);
+                    for (int mb = g; mb < ge; ++mb) {
+                        const uint4 qi = st[mb];
+                        if ((int)qi.w >= a1) break;
+                        const int i = roff + (int)qi.w, at = __builtin_amdgcn_readlane(len, mb - g);
+                        cnt = 0;
+                        test(ch, qi, base);
+                        __builtin_amdgcn_wave_barrier();
+                        for (int k = lw; k < min(cnt, a.cap - at); k += 64)
+                            a.nbr[slot_index(i, at + k, a.N)] = row[k];
+                        __builtin_amdgcn_wave_barrier();   // the row buffer is reused
+                        len += lw == mb - g ? cnt : 0;
+                    }
                 }
-                write(roff + (int)qi.w);
+                const int id = g + lw < ge ? (int)st[g + lw].w : a1;
+                if (id < a1) {
+                    const int used = min(len, a.cap), pad_end = min((used + 3) & ~3, a.cap);
+                    for (int k = used; k < pad_end; ++k) a.nbr[slot_index(roff + id, k, a.N)] = roff + id;
+                    if (len > a.cap) atomicOr(a.status, ST_NEIGH_OVERFLOW);
+                    a.nnb[roff + id] = used;
+                }
             }
         }
     }
