@@ -1251,7 +1251,6 @@ __device__ __forceinline__ void build_rows(const NeighArgs& a, const RowsGeom& g
                 st[b + rank] = make_uint4(qx[u], qy[u], qz[u], (uint32_t)k);
                 if (k >= a0 && k < a1 && (rank - lo) % share == 0)
                     work[atomicAdd(&sh_n, 1)] = (uint32_t)(b + rank) << 12 | (uint32_t)c;
-                if (m > 64) atomicOr(a.status, ST_CELL_OVERFLOW);   // only overlapping atoms crowd a cell so
             }
         } else {
 #pragma unroll

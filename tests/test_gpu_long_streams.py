@@ -99,3 +99,15 @@ def test_overflow_within_a_long_stream(lds):
     full = ctx.copy_lists()[1].cpu().numpy()
     assert (nnb == 96).all() and np.array_equal(nbr, full[:, :96])
     ctx.close()
+
+
+@pytest.mark.parametrize("atoms", [500, 1458])   # one chunk, and pieces
+def test_more_members_than_a_wavefront_in_one_cell(atoms):
+    reps = [_sites(9, atoms)]
+    rng = np.random.default_rng(6)
+    pos = I.displaced(reps[0].sites(), 0.1, seed=3)
+    crowd = rng.permutation(atoms)[:140]
+    # the crowd in the middle of one cell of edge 3.54 A (five per box edge)
+    pos[crowd] = 1.5 * reps[0].box / 5 + rng.uniform(-1.0, 1.0, (140, 3))
+    nnb = _check(reps, pos, 0.65)
+    assert nnb[crowd].min() >= 139
