@@ -539,26 +539,43 @@ void build_slices(eamfe_ctx* c)
 // 2666/2569; 10,976 atoms, 20 steps 1548/1178/922/854/913; 25,512 atoms, one
 // evaluation 116/96/89/89/95; 128,000 atoms, 20 steps 2462/2604/2986/3880/6514;
 // 113,090 atoms FP64, 10 steps 1126/1057/1176/1375/1857; 128 atoms FP64, 100
-// steps 5178/3693/2620/2034/1742.  Threads per block: FP32 512 (the table is
-// staged once for eight wavefronts; 4,096 atoms at 256/512/1024: 2703/2569/
-// 2758), 256 where the chip is filled more than four times over (1.3 million
-// atoms, 4 steps: 2661 against 2806 at 512); FP64 1024 where the tables are
-// staged in LDS (two units per CU and more; 256/512/1024: 1390/1140/1057), else
-// 64 (128 atoms at 64/128/256: 1742/1810/1898).
-void choose_launch(eamfe_ctx* c)
+// steps 5178/3693/2620/2034/1742.  FP64 stops at six wavefronts per CU for
+// sixteen lanes: 10,976 atoms, 10 steps, best block each 605/550/579 at 4/8/16.
+int auto_lanes(const eamfe_ctx* c)
 {
     const bool f32 = c->precision == EAMFE_FP32;
-    const long most = (f32 ? 10L : 14L) * c->n_cu;
     int lanes = 16;
-    while (lanes > 1 && (long)c->N * lanes / 64 > most) lanes /= 2;
-    const long waves = (long)c->N * lanes / 64;
-    c->lanes = lanes;
-    c->block = f32 ? (waves > 64L * c->n_cu ? 256 : 512) : (waves >= 2L * c->n_cu ? 1024 : 64);
+    while (lanes > 1 && (long)c->N * lanes / 64 > (f32 ? 10L : lanes == 16 ? 6L : 14L) * c->n_cu) lanes /= 2;
+    return lanes;
+}
+
+// Threads per block, for the unit table of those lanes.  FP32 512 (the table is
+// staged once for eight wavefronts; 4,096 atoms at 256/512/1024: 2703/2569/
+// 2758), 256 where the chip is filled more than four times over (1.3 million
+// atoms, 4 steps: 2661 against 2806 at 512).  FP64 with its tables in LDS,
+// where one block fits a CU: as many wavefronts as give the fullest CU's units
+// one each (10 steps at 256/512/1024 threads: 16,000 atoms, 8 lanes, 7.8 units
+// per CU 604/517/711; 32,000, 4 lanes, 7.8 1069/867/1263; 113,090, 2 lanes, 14
+// 1319/1081/997); sixteen lanes keep 1024, ahead of 4 lanes x 256 but not of
+// narrower blocks (5,488 atoms, 10 steps: 588 against 736; 464 at 512).  FP64
+// from global memory: 128 (3001 knots, at 128/256/1024: 32,000 atoms
+// 1164/1160/2047, 113,090 1404/1483/1480), 64 below two units per CU (128
+// atoms, 100 steps at 64/128/256: 1742/1810/1898).
+int auto_block(const eamfe_ctx* c)
+{
+    if (c->precision == EAMFE_FP32) return (long)c->N * c->lanes / 64 > 64L * c->n_cu ? 256 : 512;
+    if (c->n_tiles < 2 * c->n_cu) return 64;
+    if (!fp64_tables_in_lds(c->n_r, c->n_tiles, c->n_cu, (size_t)c->max_lds)) return 128;
+    if (c->lanes == 16) return 1024;
+    long most = 0;   // units of the fullest CU
+    for (int q = 0; q < c->nq; ++q)
+        most = std::max<long>(most, ((long)(c->qoff[q + 1] - c->qoff[q]) * c->nq + c->n_cu - 1) / c->n_cu);
+    return most > 12 ? 1024 : (int)std::max(4L, (most + 1) / 2 * 2) * 64;
 }
 
 int build_tiles(eamfe_ctx* c)
 {
-    if (c->auto_launch) choose_launch(c);
+    if (c->auto_launch) c->lanes = auto_lanes(c);
     const int A = 64 / c->lanes;
     c->tiles.clear();
     std::vector<std::vector<Tile>> per(c->n_rep);
@@ -603,6 +620,7 @@ int build_tiles(eamfe_ctx* c)
         c->qoff[1] = (int)c->tiles.size();
         c->nq = 1;
     }
+    if (c->auto_launch) c->block = auto_block(c);
     if ((long)c->tiles.size() > c->shape.max_units) return fail(c, EAMFE_EINVAL, "internal: unit table overflow");
     if (!c->tiles.empty())
         HIPCHK(c, hipMemcpy(c->tiles_d.p, c->tiles.data(), c->tiles.size() * sizeof(Tile), hipMemcpyHostToDevice));
@@ -1523,6 +1541,7 @@ int eam_setup(eamfe_ctx* c, int n_r, double r_cut, const double* phi, const doub
     OK(upload_tables(c));
     c->have_pot = true;
     c->have_list = false;   // the cutoff may have changed
+    if (c->n_rep && c->auto_launch) c->block = auto_block(c);   // follows the tables' size
     return EAMFE_OK;
 }
 

@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 
 namespace eamfe {
@@ -223,6 +224,18 @@ inline bool rows_lds_fit(int atoms, int cells, int cap, size_t max_lds)
 {
     const auto up = [](size_t b) { return (b + 15) & ~(size_t)15; };
     return (size_t)atoms * 16 + up((size_t)atoms * 2) + up((size_t)(cells + 1) * 4) + (size_t)cap * 16 + 1024 <= max_lds;
+}
+
+// FP64 pair kernels read their tables from LDS when the force pass's pair
+// table (64 bytes per interval) fits one block's and the launch holds at
+// least two units per compute unit; otherwise from global memory.  Staging
+// the table costs each block a fixed latency (128 KB at 2000 knots), which
+// a launch of few units, such as one replica of a few thousand atoms, does
+// not earn back: there the pass is latency bound and the table's reads
+// come from L2 at little cost.  (n_r 0: no tables yet.)
+inline bool fp64_tables_in_lds(int n_r, long units, int n_cu, size_t max_lds)
+{
+    return (size_t)std::max(0, n_r - 1) * 64 <= max_lds && units >= 2L * n_cu;
 }
 
 // Launchers (eamfe_kernels.hip).  Each returns a hipError_t as int.

@@ -2285,17 +2285,10 @@ static size_t device_lds()
     return (size_t)cached[dev];
 }
 
-// FP64 pair kernels read their tables from LDS when the force pass's pair
-// table (64 bytes per interval) fits one block's and the launch holds at
-// least two units per compute unit; otherwise from global memory.  Staging
-// the table costs each block a fixed latency (128 KB at 2000 knots), which
-// a launch of few units, such as one replica of a few thousand atoms, does
-// not earn back: there the pass is latency bound and the table's reads
-// come from L2 at little cost.
 template <typename real>
 static bool fp64_lds(const StepArgs& a)
 {
-    return sizeof(real) == 8 && a.has_eam && lds_bytes<real>(a, 2) <= device_lds() && a.n_tiles >= 2 * a.n_cu;
+    return sizeof(real) == 8 && a.has_eam && fp64_tables_in_lds(a.tab.n_r, a.n_tiles, a.n_cu, device_lds());
 }
 
 // Resident blocks per CU of a pair kernel at this block size and LDS use
