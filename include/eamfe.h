@@ -165,8 +165,9 @@ int eamfe_set_stream(eamfe_ctx* ctx, void* hip_stream);
 
 /* Launch shape of the pair kernels: lanes per atom (1, 2, 4, 8 or 16) and
  * threads per block (64..1024, multiple of 64).  0 keeps the current value.
- * Until a shape is set here or by the autotuner, eamfe_system_setup chooses
- * one from the number of atoms and the precision.
+ * Until a shape is set here or by the autotuner, the library chooses one from
+ * the number of atoms, the precision, the tables' size and whether a run has
+ * pair sums (eamfe_get_launch: that of the last setup or run).
  * In EAMFE_FP32 results are bit-identical for every shape. */
 int eamfe_set_launch(eamfe_ctx* ctx, int lanes_per_atom, int block_threads);
 int eamfe_get_launch(const eamfe_ctx* ctx, int* lanes_per_atom, int* block_threads);

@@ -84,6 +84,7 @@ struct eamfe_ctx {
     int lanes = 4;
     int block = 256;
     bool auto_launch = true;   // lanes and block follow the system's size (until set_launch or the tuner)
+    bool pair_shape = true;    // and are those of passes with pair sums (false: of the harmonic modes)
     int grid = 0;      // persistent pair-kernel blocks (0: every resident slot), a multiple of 8
     int n_cu = 256;
     int max_lds = 65536;   // LDS bytes one block may allocate
@@ -541,8 +542,13 @@ void build_slices(eamfe_ctx* c)
 // 113,090 atoms FP64, 10 steps 1126/1057/1176/1375/1857; 128 atoms FP64, 100
 // steps 5178/3693/2620/2034/1742.  FP64 stops at six wavefronts per CU for
 // sixteen lanes: 10,976 atoms, 10 steps, best block each 605/550/579 at 4/8/16.
+// The harmonic modes have no walk to shorten, and every lane beyond the first
+// adds units whose noise sums each wavefront of the replica adds up: four up to
+// 16,384 atoms (20 steps FP64 at 1/2/4/8/16: 128 atoms 381/381/387/400/428,
+// 16,000 398/410/415/437/530), one beyond (32,000: 439/482/627/912/2179).
 int auto_lanes(const eamfe_ctx* c)
 {
+    if (!c->pair_shape) return c->N <= 16384 ? 4 : 1;
     const bool f32 = c->precision == EAMFE_FP32;
     int lanes = 16;
     while (lanes > 1 && (long)c->N * lanes / 64 > (f32 ? 10L : lanes == 16 ? 6L : 14L) * c->n_cu) lanes /= 2;
@@ -561,8 +567,10 @@ int auto_lanes(const eamfe_ctx* c)
 // from global memory: 128 (3001 knots, at 128/256/1024: 32,000 atoms
 // 1164/1160/2047, 113,090 1404/1483/1480), 64 below two units per CU (128
 // atoms, 100 steps at 64/128/256: 1742/1810/1898).
+// The harmonic modes: 256 (16,000 atoms, 20 steps at 64/256/1024: 412/398/499).
 int auto_block(const eamfe_ctx* c)
 {
+    if (!c->pair_shape) return 256;
     if (c->precision == EAMFE_FP32) return (long)c->N * c->lanes / 64 > 64L * c->n_cu ? 256 : 512;
     if (c->n_tiles < 2 * c->n_cu) return 64;
     if (!fp64_tables_in_lds(c->n_r, c->n_tiles, c->n_cu, (size_t)c->max_lds)) return 128;
@@ -630,6 +638,20 @@ int build_tiles(eamfe_ctx* c)
         HIPCHK(c, hipMemcpy(c->slices_d.p, c->slices.data(), c->slices.size() * sizeof(int4), hipMemcpyHostToDevice));
     HIPCHK(c, hipMemcpy(c->reps_d.p, c->reps.data(), c->reps.size() * sizeof(RepDesc), hipMemcpyHostToDevice));
     return EAMFE_OK;
+}
+
+// The automatic shape for passes with (pair) or without pair sums; the unit
+// table is built anew where the lanes change.
+int auto_shape(eamfe_ctx* c, bool pair)
+{
+    if (!c->auto_launch || !c->n_rep || pair == c->pair_shape) return EAMFE_OK;
+    c->pair_shape = pair;
+    if (auto_lanes(c) == c->lanes) {
+        c->block = auto_block(c);
+        return EAMFE_OK;
+    }
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    return build_tiles(c);
 }
 
 int upload_reps(eamfe_ctx* c)
@@ -1271,6 +1293,7 @@ int adjoint_theta_with(eamfe_ctx* c, const double* x, const double* w_host, int 
                        unsigned long long* static_bins)
 {
     OK(check_adjoint_tables(c, "adjoint_theta"));   // before any kernel runs
+    OK(auto_shape(c, true));
     OK(pack(c, x));
     OK(ensure_lists(c, c->have_list ? c->skin : 0.3, PA(c)));
     NeighArgs na = neigh_args(c, PA(c));
@@ -1541,7 +1564,7 @@ int eam_setup(eamfe_ctx* c, int n_r, double r_cut, const double* phi, const doub
     OK(upload_tables(c));
     c->have_pot = true;
     c->have_list = false;   // the cutoff may have changed
-    if (c->n_rep && c->auto_launch) c->block = auto_block(c);   // follows the tables' size
+    if (c->n_rep && c->auto_launch && c->pair_shape) c->block = auto_block(c);   // follows the tables' size
     return EAMFE_OK;
 }
 
@@ -1615,6 +1638,7 @@ int eamfe_system_setup(eamfe_ctx* c, int n_rep, const eamfe_replica* in, const d
     HIPCHK(c, hipMemset(c->row_acc_d.p, 0, (size_t)(n_rep + 3) * sizeof(double)));
     c->have_list = false;
     c->has_kscale = false;
+    c->pair_shape = c->have_pot;
     return build_tiles(c);
 }
 
@@ -1656,6 +1680,7 @@ int eam_forces(eamfe_ctx* c, const double* x, double* f, double* U, double* e_at
     if (!ready(c, true)) return c ? EAMFE_ESTATE : EAMFE_EINVAL;
     if (!x) return fail(c, EAMFE_EINVAL, "eam_forces: null positions");
     (void)hipSetDevice(c->device);
+    OK(auto_shape(c, true));
     OK(pack(c, x));
     OK(ensure_lists(c, c->have_list ? c->skin : 0.3, PA(c)));
     for (int attempt = 0;; ++attempt) {
@@ -1694,6 +1719,7 @@ int eamfe_init_velocities(eamfe_ctx* c, double* v, int fix_com)
     if (!ready(c, false)) return c ? EAMFE_ESTATE : EAMFE_EINVAL;
     if (!v) return fail(c, EAMFE_EINVAL, "init_velocities: null v");
     (void)hipSetDevice(c->device);
+    OK(auto_shape(c, c->have_pot));   // the same units, so the same mean, whatever ran before
     StepArgs a = step_args(c);
     a.v = v;
     LCHK(c, launch_init_velocities(a, c->n_rep, fix_com, c->stream));
@@ -1737,6 +1763,7 @@ int run_range(eamfe_ctx* c, const eamfe_protocol* p, int64_t S, int64_t s0, int6
 {
     if (has_eam && c->adj_every > 0) OK(check_adjoint_tables(c, "adjoint sampling"));   // before any step runs
     drop_graphs(c);   // captured kernel arguments belong to one call (pointers, protocol, shapes)
+    OK(auto_shape(c, has_eam));
     OK(pack(c, x));
     const bool tuner = x == (double*)c->tune_x.p;   // x and v are the tuner's copies
     const auto moved = [&] {
@@ -2237,6 +2264,7 @@ int eamfe_pressure(eamfe_ctx* c, const double* x, const double* v, double* P)
     if (!ready(c, true)) return c ? EAMFE_ESTATE : EAMFE_EINVAL;
     if (!x || !P) return fail(c, EAMFE_EINVAL, "pressure: null argument");
     (void)hipSetDevice(c->device);
+    OK(auto_shape(c, true));
     OK(pack(c, x));
     OK(ensure_lists(c, c->have_list ? c->skin : 0.3, PA(c)));
     std::vector<double> part((size_t)c->n_tiles * 3);

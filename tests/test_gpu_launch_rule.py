@@ -1,7 +1,9 @@
 """The launch shape that the library chooses in EAMFE_FP64 where the caller
 sets none, at the edges of its rule (sixteen lanes or eight, units counted
 per replica, tables that fit a block's LDS or not, and tables that change
-after the system is set up): the forces are those of an explicit shape."""
+after the system is set up): the forces are those of an explicit shape.  The
+harmonic modes have a shape of their own, which leaves no trace in the runs
+with pair sums around them."""
 import numpy as np
 import pytest
 
@@ -69,3 +71,49 @@ def test_shape_follows_the_tables():
     ctx.close()
     if torch.cuda.get_device_properties(0).multi_processor_count == 256:
         assert got == [(8, 128), (8, 512), (8, 128)]
+
+
+@pytest.mark.parametrize("prec", [FP64, FP32])
+@pytest.mark.parametrize("kind,n,n_rep,harmonic", [
+    ("bcc", 4, 1, (4, 256)), ("fcc", 16, 1, (4, 256)),   # 128 and 16,384 atoms
+    ("bcc", 21, 1, (1, 256)),                            # 18,522
+])
+def test_harmonic_modes_between_runs_with_pairs(prec, kind, n, n_rep, harmonic):
+    import torch
+
+    import paper_2201_04622_amd.eamfe as E
+    reps = _reps(kind, n, n_rep, 0)
+    x0 = E.to_soa(I.batch_arrays(reps)["x0"])
+    fl, hh = E.protocol("fl", 2, 4, 0, 0), E.protocol("hh", 2, 4, 0, 0)
+    out = {}
+    for name in ("with", "without", "harmonic alone", "harmonic fixed"):
+        ctx = E.Context(0, prec)
+        if name == "harmonic fixed":
+            ctx.set_launch(*harmonic)
+        if not name.startswith("harmonic"):
+            ctx.eam_setup(I.synthetic_eam_knots())
+        ctx.system_setup(reps, x0)
+        shape = ctx.get_launch()
+
+        def run(p):
+            x, v = x0.clone(), torch.zeros_like(x0)
+            ctx.init_velocities(v, True)
+            W = torch.zeros(n_rep, 10, dtype=torch.float64, device="cuda")
+            ctx.run_switching(p, x, v, 0, 10, W_out=W)
+            return [t.cpu().numpy() for t in (x, v, W)]
+
+        if name == "with":
+            ctx.set_launch(0, 0)   # keeps the automatic shape
+            run(hh)
+            assert ctx.get_launch() == harmonic
+            out[name] = run(fl)
+            assert ctx.get_launch() == shape
+        elif name == "without":
+            out[name] = run(fl)
+        else:
+            assert shape == harmonic
+            out[name] = run(hh)
+        ctx.close()
+    for a, b in (("with", "without"), ("harmonic alone", "harmonic fixed")):
+        for u, w in zip(out[a], out[b]):
+            assert np.array_equal(u, w)
