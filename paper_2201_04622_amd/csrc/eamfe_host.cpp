@@ -581,6 +581,15 @@ int auto_block(const eamfe_ctx* c)
     return most > 12 ? 1024 : (int)std::max(4L, (most + 1) / 2 * 2) * 64;
 }
 
+int upload_reps(eamfe_ctx* c)
+{
+    HIPCHK(c, hipMemcpyAsync(c->reps_d.p, c->reps.data(), c->reps.size() * sizeof(RepDesc), hipMemcpyHostToDevice,
+                             c->stream));
+    // the host vector may change before the copy runs: wait for it
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    return EAMFE_OK;
+}
+
 int build_tiles(eamfe_ctx* c)
 {
     if (c->auto_launch) c->lanes = auto_lanes(c);
@@ -630,14 +639,15 @@ int build_tiles(eamfe_ctx* c)
     }
     if (c->auto_launch) c->block = auto_block(c);
     if ((long)c->tiles.size() > c->shape.max_units) return fail(c, EAMFE_EINVAL, "internal: unit table overflow");
-    if (!c->tiles.empty())
-        HIPCHK(c, hipMemcpy(c->tiles_d.p, c->tiles.data(), c->tiles.size() * sizeof(Tile), hipMemcpyHostToDevice));
     build_slices(c);
     if ((long)c->slices.size() > c->shape.max_slices) return fail(c, EAMFE_EINVAL, "internal: slice table overflow");
+    if (!c->tiles.empty())
+        HIPCHK(c, hipMemcpyAsync(c->tiles_d.p, c->tiles.data(), c->tiles.size() * sizeof(Tile), hipMemcpyHostToDevice,
+                                 c->stream));
     if (!c->slices.empty())
-        HIPCHK(c, hipMemcpy(c->slices_d.p, c->slices.data(), c->slices.size() * sizeof(int4), hipMemcpyHostToDevice));
-    HIPCHK(c, hipMemcpy(c->reps_d.p, c->reps.data(), c->reps.size() * sizeof(RepDesc), hipMemcpyHostToDevice));
-    return EAMFE_OK;
+        HIPCHK(c, hipMemcpyAsync(c->slices_d.p, c->slices.data(), c->slices.size() * sizeof(int4),
+                                 hipMemcpyHostToDevice, c->stream));
+    return upload_reps(c);   // waits for all three
 }
 
 // The automatic shape for passes with (pair) or without pair sums; the unit
@@ -652,15 +662,6 @@ int auto_shape(eamfe_ctx* c, bool pair)
     }
     HIPCHK(c, hipStreamSynchronize(c->stream));
     return build_tiles(c);
-}
-
-int upload_reps(eamfe_ctx* c)
-{
-    HIPCHK(c, hipMemcpyAsync(c->reps_d.p, c->reps.data(), c->reps.size() * sizeof(RepDesc), hipMemcpyHostToDevice,
-                             c->stream));
-    // the host vector may change before the copy runs: wait for it
-    HIPCHK(c, hipStreamSynchronize(c->stream));
-    return EAMFE_OK;
 }
 
 double4* PA(eamfe_ctx* c) { return (double4*)c->Pa_d.p; }
@@ -1622,20 +1623,24 @@ int eamfe_system_setup(eamfe_ctx* c, int n_rep, const eamfe_replica* in, const d
         off += q.n_atoms;
     }
     const size_t v3 = 3 * (size_t)N * sizeof(double);
-    HIPCHK(c, hipMemcpy(c->x0_d.p, x0_dev, v3, hipMemcpyDeviceToDevice));
-    HIPCHK(c, hipMemcpy(c->xref_d.p, x0_dev, v3, hipMemcpyDeviceToDevice));
-    HIPCHK(c, hipMemset(c->xi_d.p, 0, v3));
-    HIPCHK(c, hipMemset(c->Pa_d.p, 0, (size_t)N * sizeof(double4)));
-    HIPCHK(c, hipMemset(c->Pb_d.p, 0, (size_t)N * sizeof(double4)));
-    HIPCHK(c, hipMemset(c->Qa_d.p, 0, (size_t)N * sizeof(uint4)));
-    HIPCHK(c, hipMemset(c->Qb_d.p, 0, (size_t)N * sizeof(uint4)));
-    HIPCHK(c, hipMemset(c->e_emb_d.p, 0, (size_t)N * sizeof(double)));
-    HIPCHK(c, hipMemcpy(c->rep_of_d.p, rep_of.data(), (size_t)N * sizeof(int32_t), hipMemcpyHostToDevice));
-    HIPCHK(c, hipMemset(c->U_rep_d.p, 0, (size_t)n_rep * 2 * sizeof(double)));
-    HIPCHK(c, hipMemset(c->W_state_d.p, 0, (size_t)n_rep * sizeof(double)));
-    HIPCHK(c, hipMemset(c->rebuild_d.p, 0, (size_t)n_rep * sizeof(int32_t)));
-    HIPCHK(c, hipMemset(c->flag_pre_d.p, 0, (size_t)(2 * n_rep + 2) * sizeof(int32_t)));
-    HIPCHK(c, hipMemset(c->row_acc_d.p, 0, (size_t)(n_rep + 3) * sizeof(double)));
+    // in order with the context's stream (build_tiles waits for all of it), and
+    // after work on the null stream, which may have written x0
+    HIPCHK(c, hipStreamSynchronize(nullptr));
+    HIPCHK(c, hipMemcpyAsync(c->x0_d.p, x0_dev, v3, hipMemcpyDeviceToDevice, c->stream));
+    HIPCHK(c, hipMemcpyAsync(c->xref_d.p, x0_dev, v3, hipMemcpyDeviceToDevice, c->stream));
+    HIPCHK(c, hipMemsetAsync(c->xi_d.p, 0, v3, c->stream));
+    HIPCHK(c, hipMemsetAsync(c->Pa_d.p, 0, (size_t)N * sizeof(double4), c->stream));
+    HIPCHK(c, hipMemsetAsync(c->Pb_d.p, 0, (size_t)N * sizeof(double4), c->stream));
+    HIPCHK(c, hipMemsetAsync(c->Qa_d.p, 0, (size_t)N * sizeof(uint4), c->stream));
+    HIPCHK(c, hipMemsetAsync(c->Qb_d.p, 0, (size_t)N * sizeof(uint4), c->stream));
+    HIPCHK(c, hipMemsetAsync(c->e_emb_d.p, 0, (size_t)N * sizeof(double), c->stream));
+    HIPCHK(c, hipMemcpyAsync(c->rep_of_d.p, rep_of.data(), (size_t)N * sizeof(int32_t), hipMemcpyHostToDevice,
+                             c->stream));
+    HIPCHK(c, hipMemsetAsync(c->U_rep_d.p, 0, (size_t)n_rep * 2 * sizeof(double), c->stream));
+    HIPCHK(c, hipMemsetAsync(c->W_state_d.p, 0, (size_t)n_rep * sizeof(double), c->stream));
+    HIPCHK(c, hipMemsetAsync(c->rebuild_d.p, 0, (size_t)n_rep * sizeof(int32_t), c->stream));
+    HIPCHK(c, hipMemsetAsync(c->flag_pre_d.p, 0, (size_t)(2 * n_rep + 2) * sizeof(int32_t), c->stream));
+    HIPCHK(c, hipMemsetAsync(c->row_acc_d.p, 0, (size_t)(n_rep + 3) * sizeof(double), c->stream));
     c->have_list = false;
     c->has_kscale = false;
     c->pair_shape = c->have_pot;
