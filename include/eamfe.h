@@ -168,7 +168,11 @@ int eamfe_set_stream(eamfe_ctx* ctx, void* hip_stream);
  * Until a shape is set here or by the autotuner, the library chooses one from
  * the number of atoms, the precision, the tables' size and whether a run has
  * pair sums (eamfe_get_launch: that of the last setup or run).
- * In EAMFE_FP32 results are bit-identical for every shape. */
+ * In EAMFE_FP32 results are bit-identical for every shape.  In EAMFE_FP64 (and
+ * in EAMFE_FP32 without the deterministic sums) the order of a replica's sums
+ * follows the shape, so with the library's choice its last bits depend on how
+ * many atoms the other replicas of the context hold; with a shape set here they
+ * do not. */
 int eamfe_set_launch(eamfe_ctx* ctx, int lanes_per_atom, int block_threads);
 int eamfe_get_launch(const eamfe_ctx* ctx, int* lanes_per_atom, int* block_threads);
 
@@ -381,7 +385,8 @@ int eamfe_system_setup(eamfe_ctx* ctx, int n_rep, const eamfe_replica* reps, con
  * (rounded up to a multiple of 32): a row that does not fit is reported as
  * EAMFE_ENEIGH_OVERFLOW.  With max_neighbors = 0 the capacity is estimated
  * from the densest replica and enlarged until every row (and cell bin) of
- * this configuration fits.  EAMFE_EBOX if an edge <= 2(r_cut+skin). */
+ * this configuration fits.  Lists that any call reports as overflowed are
+ * built again by the next pass that uses them.  EAMFE_EBOX if an edge <= 2(r_cut+skin). */
 int neigh_build(eamfe_ctx* ctx, const double* x_dev, double skin, int max_neighbors);
 
 /* ---- evaluation -------------------------------------------------------- */

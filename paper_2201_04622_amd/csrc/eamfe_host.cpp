@@ -1972,7 +1972,7 @@ int eamfe_adjoint_theta_noalloc(eamfe_ctx* c, const double* x, const double* w_h
         return fail(c, EAMFE_EDEVICE, "adjoint_theta_noalloc: no scratch address for this device");
     const size_t nb = (size_t)std::max(c->n_r, c->n_rho) - 1;
     const size_t bins = (size_t)c->n_rep * 3 * nb * 4 * sizeof(unsigned long long);
-    // the region's documented limit counts knot-transform rows besides the bins
+    // the documented limit holds room for knot-transform rows besides the bins (none are used now)
     const size_t fin = (size_t)(reduce ? 1 : c->n_rep) * 3 * 2 * (nb + 1) * sizeof(double);
     const size_t fin_off = (bins + 255) / 256 * 256;
     if (fin_off + fin > kNoAllocScratchBytes)

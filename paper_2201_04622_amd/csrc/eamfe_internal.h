@@ -82,7 +82,7 @@ struct NeighArgs {
     int32_t* nbr;               // [N][cap] global atom ids
     int32_t* nnb;               // [N]
     int32_t* rebuild;           // [n_rep] flags
-    int32_t* flag_pre;          // [2 (n_rep + 1)] prefix of flagged atoms, then of flagged cells
+    int32_t* flag_pre;          // [2 (n_rep + 1)] prefix of flagged atoms, then of the row builder's items
     int32_t* status;
     int N, n_cells, ccap, cap;
     int chunk;                  // candidates staged per wavefront in the row builder (>= ccap)
@@ -267,7 +267,6 @@ int launch_adjoint_finish(const AdjointArgs& a, const double* w, int reduce, dou
 // Rows in [N][out_cap] row-major order (slots past the row length = -1).
 int launch_rows_rowmajor(const int32_t* nbr, const int32_t* nnb, int N, int cap, int32_t* out, int out_cap,
                          hipStream_t s);
-int launch_rho(const StepArgs& a, double* rho_out, int precision, int lanes, int block, hipStream_t s);
 // p[0 .. n) = v (a fill kernel, so that the clearing can sit inside a captured graph)
 int launch_fill_u64(unsigned long long* p, size_t n, unsigned long long v, hipStream_t s);
 
