@@ -62,11 +62,13 @@ struct Shape {
     long n_r = 0, n_rho = 0;
     long cap = 0, n_cells = 0, ccap = 0;
     long lam_len = 0;      // entries of the lambda table
+    long adj_rows = 0;     // rows of knot gradients kept at a chunk's start (0: never sampled in a run)
 
     bool operator==(const Shape& o) const
     {
         return N == o.N && n_rep == o.n_rep && max_units == o.max_units && max_slices == o.max_slices && n_r == o.n_r &&
-               n_rho == o.n_rho && cap == o.cap && n_cells == o.n_cells && ccap == o.ccap && lam_len == o.lam_len;
+               n_rho == o.n_rho && cap == o.cap && n_cells == o.n_cells && ccap == o.ccap && lam_len == o.lam_len &&
+               adj_rows == o.adj_rows;
     }
 };
 
@@ -159,7 +161,7 @@ struct eamfe_ctx {
     int64_t chunk = 1000;
     int min_ccap = 0;
     int64_t replays = 0;
-    DevBuf snap_P, snap_Q, snap_v, snap_w, snap_rows;
+    DevBuf snap_P, snap_Q, snap_v, snap_w, snap_rows, snap_adj;
 
     // adjoint: densities, fixed-point bins, weights
     DevBuf rho_d, bins_d, adj_w_d;
@@ -302,6 +304,7 @@ void for_regions(eamfe_ctx* c, const Shape& s, F&& f)
     if (N && s.n_r) {
         const size_t nb = (size_t)std::max(s.n_r, s.n_rho) - 1;
         f(c->bins_d, G_ADJ, R * 3 * nb * 4 * sizeof(unsigned long long));
+        if (s.adj_rows) f(c->snap_adj, G_ADJ, (size_t)s.adj_rows * 3 * (nb + 1) * d);
     }
 }
 
@@ -1233,6 +1236,12 @@ int capture_middle(eamfe_ctx* c, const StepArgs& a0, double4* start, bool has_ea
     return EAMFE_OK;
 }
 
+// Whether step it is one whose knot gradient a run samples.
+bool adjoint_due(const eamfe_ctx* c, int64_t it)
+{
+    return c->adj_every > 0 && it % c->adj_every == 0 && c->lam_valid && c->lam_h[it] == c->lam_h[0];
+}
+
 // Iterations it_first .. it_last of a protocol starting from packed
 // positions *cur (one of the two internal buffers); on return *cur is the
 // buffer holding the final positions.  The first and last iterations carry
@@ -1269,8 +1278,7 @@ int iterate(eamfe_ctx* c, StepArgs a, double4** cur_io, bool has_eam, int64_t it
             base += reps * c->graph_iters;   // each replay advanced the counter
             continue;
         }
-        const bool sample = has_eam && c->adj_every > 0 && it < it_last && it % c->adj_every == 0 &&
-                            c->lam_valid && c->lam_h[it] == c->lam_h[0];
+        const bool sample = has_eam && it < it_last && adjoint_due(c, it);
         a.it_k = it - base;
         OK(one_iteration(c, a, cur, nxt, has_eam, c->stream, sample, has_eam && it > it_first));
         std::swap(cur, nxt);
@@ -1592,6 +1600,7 @@ int eamfe_system_setup(eamfe_ctx* c, int n_rep, const eamfe_replica* in, const d
     for (int r = 0; r < n_rep; ++r) s2.max_units += (in[r].n_atoms + 3) / 4;
     s2.max_slices = 8L * std::max<long>(n_rep, c->n_cu);
     s2.cap = s2.n_cells = s2.ccap = 0;   // lists are planned for the new system
+    s2.adj_rows = 0;
     OK(bind(c, s2));   // nothing changes if the system does not fit
     c->have_list = false;
     c->cap_min = 0;
@@ -1769,7 +1778,6 @@ int run_range(eamfe_ctx* c, const eamfe_protocol* p, int64_t S, int64_t s0, int6
     if (has_eam && c->adj_every > 0) OK(check_adjoint_tables(c, "adjoint sampling"));   // before any step runs
     drop_graphs(c);   // captured kernel arguments belong to one call (pointers, protocol, shapes)
     OK(auto_shape(c, has_eam));
-    OK(pack(c, x));
     const bool tuner = x == (double*)c->tune_x.p;   // x and v are the tuner's copies
     const auto moved = [&] {
         if (!tuner) return;
@@ -1777,6 +1785,24 @@ int run_range(eamfe_ctx* c, const eamfe_protocol* p, int64_t S, int64_t s0, int6
         v = (double*)c->tune_v.p;
     };
     c->resume_step = s0;   // nothing has run if the lists do not fit
+    // a replayed chunk's knot-gradient samples count once: what the caller's
+    // buffer holds at the start of a chunk with samples is kept
+    const auto samples = [&](int64_t b, int64_t e) {
+        if (!has_eam || c->adj_every <= 0) return false;
+        for (int64_t it = (b + c->adj_every - 1) / c->adj_every * c->adj_every; it < e; it += c->adj_every)
+            if (adjoint_due(c, it)) return true;
+        return false;
+    };
+    const long adj_rows = c->adj_reduce ? 1 : c->n_rep;
+    if (samples(s0, s1) && adj_rows > c->shape.adj_rows) {
+        Shape s2 = c->shape;
+        s2.adj_rows = adj_rows;
+        OK(bind(c, s2));
+        moved();
+    }
+    const size_t adj_bytes = (size_t)adj_rows * 3 * c->n_r * sizeof(double);
+    int64_t adj_samples = c->adj_samples;
+    OK(pack(c, x));
     if (has_eam) OK(ensure_lists(c, p->skin, PA(c)));
     c->resume_step = -1;
     moved();
@@ -1788,6 +1814,7 @@ int run_range(eamfe_ctx* c, const eamfe_protocol* p, int64_t S, int64_t s0, int6
     c->last_status = -1;
     for (int64_t b = s0; b < s1; b += c->chunk) {
         const int64_t e = std::min(s1, b + c->chunk);
+        const bool sampling = samples(b, e);
         if (has_eam) {
             if (b > s0) {   // (the first chunk's positions are still the caller's x)
                 HIPCHK(c, hipMemcpyAsync(c->snap_P.p, cur, p4, hipMemcpyDeviceToDevice, c->stream));
@@ -1797,6 +1824,9 @@ int run_range(eamfe_ctx* c, const eamfe_protocol* p, int64_t S, int64_t s0, int6
             HIPCHK(c, hipMemcpyAsync(c->snap_w.p, c->W_state_d.p, wb, hipMemcpyDeviceToDevice, c->stream));
             HIPCHK(c, hipMemcpyAsync(c->snap_rows.p, c->row_acc_d.p, wb + 3 * sizeof(double), hipMemcpyDeviceToDevice,
                                      c->stream));
+            if (sampling)
+                HIPCHK(c, hipMemcpyAsync(c->snap_adj.p, c->adj_out, adj_bytes, hipMemcpyDeviceToDevice, c->stream));
+            adj_samples = c->adj_samples;
         }
         for (int attempt = 0;; ++attempt) {
             StepArgs a = step_args(c);
@@ -1832,6 +1862,9 @@ int run_range(eamfe_ctx* c, const eamfe_protocol* p, int64_t S, int64_t s0, int6
             HIPCHK(c, hipMemcpyAsync(c->W_state_d.p, c->snap_w.p, wb, hipMemcpyDeviceToDevice, c->stream));
             HIPCHK(c, hipMemcpyAsync(c->row_acc_d.p, c->snap_rows.p, wb + 3 * sizeof(double), hipMemcpyDeviceToDevice,
                                      c->stream));
+            if (sampling)
+                HIPCHK(c, hipMemcpyAsync(c->adj_out, c->snap_adj.p, adj_bytes, hipMemcpyDeviceToDevice, c->stream));
+            c->adj_samples = adj_samples;
             ++c->replays;
             const int g = grow_lists(c, st);
             if (g == EAMFE_ENOMEM) {
@@ -1849,6 +1882,8 @@ int run_range(eamfe_ctx* c, const eamfe_protocol* p, int64_t S, int64_t s0, int6
             OK(g);
             moved();
             cur = start_b ? PB(c) : PA(c);
+            if (sampling)   // (its group follows the lists' and moved with them)
+                HIPCHK(c, hipMemcpyAsync(c->snap_adj.p, c->adj_out, adj_bytes, hipMemcpyDeviceToDevice, c->stream));
             OK(set_rebuild_all(c));
         }
     }

@@ -269,8 +269,8 @@ __device__ __forceinline__ Nb<kQ> gather(const double4* P, const uint4* Q, int q
 // Records from global memory: a load instruction costs one L1 access per
 // 128-byte line that four neighbouring lanes touch, and the atoms of four lanes
 // rarely share a line at one slot (3.4 lines on average), so the walk is bound
-// by these accesses: 1.3 million atoms, rows of 77, FP32 density pass 216 us,
-// 106 million accesses = 79 % of its clocks (VALU 46 %).  Four lanes reading
+// by these accesses: 1.3 million atoms, rows of 77, FP32 density pass 226 us,
+// 106 million accesses = 76 % of its clocks (VALU 45 %).  Four lanes reading
 // one row's four slots would touch 2.8 lines and have to transpose the
 // records; in FP64 two lanes sharing both halves of their records (half the
 // accesses, same bits) took 995 us where this takes 964.
