@@ -2088,8 +2088,9 @@ int eamfe_autotune(eamfe_ctx* c, const eamfe_protocol* p, int64_t step, const do
     const size_t v3 = 3 * (size_t)c->N * sizeof(double);
     HIPCHK(c, hipMemcpyAsync(c->tune_w.p, c->W_state_d.p, (size_t)c->n_rep * sizeof(double),
                              hipMemcpyDeviceToDevice, c->stream));
-    const int timing = c->timing;
+    const int timing = c->timing, adj_every = c->adj_every;
     c->timing = 0;
+    c->adj_every = 0;   // trial steps are no samples
     const int lanes0 = c->lanes, block0 = c->block, grid0 = c->grid;
     const bool auto0 = c->auto_launch;
     c->auto_launch = false;   // the trials set the shape
@@ -2225,6 +2226,7 @@ done:
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     c->timing = timing;
+    c->adj_every = adj_every;
     c->lanes = rc ? lanes0 : best_l;
     c->block = rc ? block0 : best_b;
     c->grid = rc ? grid0 : best_g;

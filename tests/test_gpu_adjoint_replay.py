@@ -46,3 +46,25 @@ def test_samples_of_a_replayed_chunk_count_once(workspace, reduce, prec, chunk, 
     assert out[0][2] == out[1][2] == 20
     for a, b in zip(out[0][:2], out[1][:2]):
         assert np.linalg.norm(a - b) <= tol * np.linalg.norm(b)
+
+
+def test_tuner_takes_no_samples():
+    import torch
+
+    import paper_2201_04622_amd.eamfe as E
+    reps = [I.Replica("bcc", 6, I.A_BCC_STABLE, 300.0, 5.0, 3)]
+    ctx = E.Context(0, FP32)
+    ctx.eam_setup(I.synthetic_eam_knots())
+    x = E.to_soa(I.batch_arrays(reps)["x0"])
+    ctx.system_setup(reps, x)
+    v = torch.zeros_like(x)
+    ctx.init_velocities(v, True)
+    ctx.neigh_build(x, 0.3, 0)
+    d = torch.zeros(1, 3, I.N_KNOTS, dtype=torch.float64, device="cuda")
+    ctx.set_adjoint_sampling(2, d)
+    p = E.protocol("fl", 200, 10, 0, 0)
+    ctx.autotune(p, 0, x, v, trial_steps=2)
+    assert ctx.adjoint_samples() == 0 and float(d.abs().max()) == 0.0
+    ctx.run_switching(p, x, v, 0, 10)
+    assert ctx.adjoint_samples() == 5 and float(d.abs().max()) > 0.0
+    ctx.close()
