@@ -1194,8 +1194,11 @@ int one_iteration(eamfe_ctx* c, StepArgs& a, double4* cur, double4* nxt, bool ha
     return EAMFE_OK;
 }
 
+// Replays still in flight (a call that was not asked to wait may leave some)
+// end before their graph goes.
 void drop_graphs(eamfe_ctx* c)
 {
+    if (c->gexec[0] || c->gexec[1]) (void)hipStreamSynchronize(c->gstream);
     for (int k = 0; k < 2; ++k) {
         if (c->gexec[k]) (void)hipGraphExecDestroy(c->gexec[k]);
         c->gexec[k] = nullptr;

@@ -2,7 +2,8 @@
 rows overflow and which clear the latched status and try again give bitwise
 what they give on the default stream, a latched condition is reported once,
 and buffers moved to a larger workspace or copied out are complete when the
-call returns."""
+call returns.  Graph replays that a call leaves in flight end before the next
+call drops their graph."""
 import numpy as np
 import pytest
 
@@ -69,4 +70,30 @@ def test_retries_on_a_side_stream(prec):
         got = _calls(prec)
     s.synchronize()
     for a, b in zip(ref, got):
+        assert np.array_equal(a, b)
+
+
+def test_graph_replays_left_in_flight():
+    # harmonic runs that are not waited for, one after another: each drops the graphs of the one before
+    import torch
+
+    import paper_2201_04622_amd.eamfe as E
+    reps = [I.Replica("bcc", 10, I.A_BCC_STABLE, 300.0, 5.0, 1 + q, k2=4.0) for q in range(4)]
+    x0 = E.to_soa(I.batch_arrays(reps)["x0"])
+    p = E.protocol("hh", 20, 200, 20, 0)
+    out = []
+    for graph in (0, 8):
+        ctx = E.Context(0, FP64)
+        ctx.set_launch(4, 256)
+        ctx.system_setup(reps, x0)
+        ctx.set_graph(graph)
+        x, v = x0.clone(), torch.zeros_like(x0)
+        ctx.init_velocities(v, True)
+        W = torch.zeros(4, 440, dtype=torch.float64, device="cuda")
+        for s in range(0, 440, 55):
+            ctx.run_switching(p, x, v, s, s + 55, W_out=W, sync=False)
+        ctx.check()
+        out.append([t.cpu().numpy() for t in (x, v, W)])
+        ctx.close()
+    for a, b in zip(*out):
         assert np.array_equal(a, b)
